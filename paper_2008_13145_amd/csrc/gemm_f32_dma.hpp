@@ -56,55 +56,17 @@ __device__ __forceinline__ int f32_mswz(int k) {
   else return CPR >= 16 ? ((k / (BK / 2)) & 1) * 8 : 0;
 }
 
-template <int BM, int BN, int T, int BK, int TA, int TB>
-__device__ __forceinline__ void f32_dma_issue(const GemmArgs& args, const char* __restrict__ Ag,
-                                              const char* __restrict__ Bg, int64_t m0, int64_t n0,
-                                              int64_t k0, char* stage, int wave, int lane) {
-  using Cfg = F32DmaCfg<BM, BN, T, BK, TA, TB>;
-  constexpr int CE = 4;
-#pragma unroll
-  for (int i = 0; i < Cfg::NW_HI; ++i) {
-    const int q = wave + i * Cfg::WAVES;
-    if (q >= Cfg::NBLK) break;   // wave-uniform
-    const bool isA = q < Cfg::NBA;
-    const int blk = isA ? q : q - Cfg::NBA;
-    const int o = blk * 1024 + lane * 16;
-    const bool kmajor = isA ? (TA == 0) : (TB == 1);
-    const int cols = isA ? BM : BN;
-    const int64_t lim = isA ? args.M : args.N;
-    const int64_t ld = isA ? args.lda : args.ldb;
-    const int64_t c0 = isA ? m0 : n0;
-    const char* base = isA ? Ag : Bg;
-    int64_t elem;
-    if (kmajor) {
-      constexpr int ROWB = BK * 4;
-      const int r = o / ROWB, p = (o % ROWB) / 16;
-      const int c = p ^ kswz<Cfg::KCPR>(r);
-      int64_t row = c0 + r;
-      row = row < lim ? row : lim - 1;
-      int64_t kk = k0 + (int64_t)c * CE;
-      kk = kk < args.K ? kk : ((args.K - 1) / CE) * CE;
-      elem = row * ld + kk;
-    } else {
-      const int ROWB = cols * 4, CPR = ROWB / 16;
-      const int k = o / ROWB, p = (o % ROWB) / 16;
-      int c;
-      if (isA) c = p ^ f32_mswz<BM / 4, BK, T>(k);
-      else c = p ^ f32_mswz<BN / 4, BK, T>(k);
-      int64_t kr = k0 + k;
-      kr = kr < args.K ? kr : args.K - 1;
-      int64_t col = c0 + (int64_t)c * CE;
-      col = col < lim ? col : ((lim - 1) / CE) * CE;
-      elem = kr * ld + col;
-    }
-    char* dst = stage + (isA ? 0 : Cfg::A_BYTES) + blk * 1024;
-    __builtin_amdgcn_global_load_lds((gbl_void_t*)(base + elem * 4), (lds_void_t*)dst, 16, 0, 0);
-  }
-}
+template <int BM, int BN, int T, int BK>
+struct F32Swz {
+  __device__ __forceinline__ static int k(int r) { return kswz<BK / 4>(r); }
+  __device__ __forceinline__ static int mn_a(int r) { return f32_mswz<BM / 4, BK, T>(r); }
+  __device__ __forceinline__ static int mn_b(int r) { return f32_mswz<BN / 4, BK, T>(r); }
+};
 
 template <int BM, int BN, int T, int BK, int TA, int TB>
 __device__ __forceinline__ void f32_dma_zero_tail(char* stage, int kvalid, int tid) {
   using Cfg = F32DmaCfg<BM, BN, T, BK, TA, TB>;
+  asm volatile("" : "+s"(kvalid));   // keeps this rarely run arithmetic out of the stage loop's preheader
 #pragma unroll
   for (int op = 0; op < 2; ++op) {
     const bool kmajor = op == 0 ? (TA == 0) : (TB == 1);
@@ -143,16 +105,19 @@ gemm_f32_dma_kernel(GemmArgs args) {
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = Cfg::WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t lds0 = lds_address(lds);
   const int wm0 = (wave / Cfg::Base::WAVES_N) * WT;
   const int wn0 = (wave % Cfg::Base::WAVES_N) * WT;
   int tm, tn;
   int64_t bz;
-  block_coords(blockIdx.x, args.tiles_m, args.tiles_n, args.batch, tm, tn, bz);
+  load_args(args);
+  block_coords(blockIdx.x, args, tm, tn, bz);
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
   const int64_t M = args.M, N = args.N, K = args.K;
-  const char* __restrict__ Ag = static_cast<const char*>(args.A) + bz * args.sA * 4;
-  const char* __restrict__ Bg = static_cast<const char*>(args.B) + bz * args.sB * 4;
+  DmaSource<Cfg, 4, BM, BN, BK, TA, TB, F32Swz<BM, BN, T, BK>> src;
+  src.init(args, static_cast<const char*>(args.A) + bz * args.sA * 4,
+           static_cast<const char*>(args.B) + bz * args.sB * 4, m0, n0, wave, lane);
 
   auto A_at = [&](const float* t, int m, int k) {
     if constexpr (TA == 0) return f32_at_kmajor<BK>(t, m, k);
@@ -186,11 +151,9 @@ gemm_f32_dma_kernel(GemmArgs args) {
   const int nk = (int)((K + BK - 1) / BK);
   const int my_blocks = (wave < Cfg::NBLK % Cfg::WAVES || Cfg::NBLK % Cfg::WAVES == 0)
                             ? Cfg::NW_HI : Cfg::NW_LO;
-#pragma unroll
+#pragma nounroll
   for (int s = 0; s < NS - 1; ++s)
-    if (s < nk)
-      f32_dma_issue<BM, BN, T, BK, TA, TB>(args, Ag, Bg, m0, n0, (int64_t)s * BK,
-                                           lds + s * Cfg::STAGE, wave, lane);
+    if (s < nk) src.issue(args, m0, n0, lds0 + s * Cfg::STAGE);
 
   for (int kt = 0; kt < nk; ++kt) {
     const int ahead = min(NS - 2, nk - 1 - kt);
@@ -202,8 +165,7 @@ gemm_f32_dma_kernel(GemmArgs args) {
       vm_wait_barrier<0>();
     }
     if (kt + NS - 1 < nk)
-      f32_dma_issue<BM, BN, T, BK, TA, TB>(args, Ag, Bg, m0, n0, (int64_t)(kt + NS - 1) * BK,
-                                           lds + ((kt + NS - 1) % NS) * Cfg::STAGE, wave, lane);
+      src.issue(args, m0, n0, lds0 + ((kt + NS - 1) % NS) * Cfg::STAGE);
     const float* as = reinterpret_cast<const float*>(cur);
     const float* bs = reinterpret_cast<const float*>(cur + Cfg::A_BYTES);
     if constexpr (T == 2) {

@@ -471,7 +471,8 @@ gemm_lp_kernel(GemmArgs args) {
   __shared__ __attribute__((aligned(16))) E lds[Cfg::LDS_BYTES / EB];
   int tm, tn;
   int64_t bz;
-  block_coords(blockIdx.x, args.tiles_m, args.tiles_n, args.batch, tm, tn, bz);
+  load_args(args);
+  block_coords(blockIdx.x, args, tm, tn, bz);
   lp_tile<EB, BM, BN, T, BK, TA, TB>(args, tm, tn, bz, lds);
 }
 

@@ -39,6 +39,11 @@ typedef __attribute__((address_space(1))) void gbl_void_t;
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef int i32x2 __attribute__((ext_vector_type(2)));
 
+// LDS byte address of a pointer into a workgroup's shared array.
+__device__ __forceinline__ uint32_t lds_address(const void* p) {
+  return __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(lds_void_t*)p);
+}
+
 // Wait until at most N of this wave's vector-memory operations (the LDS DMA
 // of later stages) are outstanding and its LDS reads have returned, then
 // meet the other waves.  One asm block, so nothing is moved across it.
@@ -56,10 +61,30 @@ __device__ __forceinline__ void vm_wait_barrier() {
 // fragment reads.  Every wait on these transfers is the explicit one of the
 // stage pipeline (vm_wait_barrier); vector-memory operations complete in
 // issue order, so the compiler's own vmcnt waits stay correct.
-__device__ __forceinline__ void lds_dma16(const void* src, void* dst) {
-  const uint32_t m0 = __builtin_amdgcn_readfirstlane(
-      (uint32_t)(uintptr_t)(lds_void_t*)dst);
+__device__ __forceinline__ void lds_dma16(const void* src, uint32_t m0) {
   asm volatile("s_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "{m0}"(m0));
+}
+
+// The same with a wave-uniform base, a 32-bit byte offset per lane and the
+// LDS address in a scalar.  The base is moved inside the block: a vector
+// memory instruction may not read a scalar register within five wait states
+// of a vector instruction's write (a readfirstlane, a spilled scalar read
+// back with readlane), a hazard the compiler does not look for in inline asm;
+// a scalar move waits for such a write by itself, and stands between the
+// write of M0 and its use.
+__device__ __forceinline__ void lds_dma16(const void* base, uint32_t off, uint32_t m0) {
+  uint64_t t;
+  asm volatile("s_mov_b64 %0, %2\n\tglobal_load_lds_dwordx4 %1, %0"
+               : "=&s"(t)
+               : "v"(off), "s"(base), "{m0}"(m0));
+}
+
+// A pointer whose value is the same in every lane, in scalar registers.
+__device__ __forceinline__ const char* uniform_ptr(const char* p) {
+  const uint64_t v = (uint64_t)(uintptr_t)p;
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<const char*>((uintptr_t)(((uint64_t)hi << 32) | lo));
 }
 
 template <int EB, int BM, int BN, int T, int BK, int TA, int TB>
@@ -117,60 +142,156 @@ __device__ __forceinline__ int mswz(int k) {
   return ((k / RP) * W) % CPR;
 }
 
-// Issue this wave's DMA blocks of one stage.  Block q of the stage (0 ..
-// NBA-1: A, then B) is handled by wave q % WAVES.  Rows / columns beyond the
-// operand are clamped to in-range addresses.
-template <int EB, int BM, int BN, int T, int BK, int TA, int TB>
-__device__ __forceinline__ void lp_dma_issue(const GemmArgs& args, const char* __restrict__ Ag,
-                                             const char* __restrict__ Bg, int64_t m0, int64_t n0,
-                                             int64_t k0, char* stage, int wave, int lane) {
-  using Cfg = LpDmaCfg<EB, BM, BN, T, BK, TA, TB>;
-  constexpr int CE = 16 / EB;   // elements per chunk
-#pragma unroll
-  for (int i = 0; i < Cfg::NW_HI; ++i) {
-    const int q = wave + i * Cfg::WAVES;
-    if (q >= Cfg::NBLK) break;   // wave-uniform
-    const bool isA = q < Cfg::NBA;
-    const int blk = isA ? q : q - Cfg::NBA;
-    const int o = blk * 1024 + lane * 16;   // byte offset in the operand's stage tile
-    const bool kmajor = isA ? (TA == 0) : (TB == 1);
-    const int rows_c = isA ? BM : BN;        // M or N extent of the tile
-    const int64_t lim = isA ? args.M : args.N;
-    const int64_t ld = isA ? args.lda : args.ldb;
-    const int64_t c0 = isA ? m0 : n0;
-    const char* base = isA ? Ag : Bg;
-    int64_t elem;   // element offset of the 16-byte chunk in the operand
+// Where a wave's DMA blocks of one stage come from.  Block q of the stage
+// (0 .. NBA-1: A, then B) is handled by wave q % WAVES; rows / columns beyond
+// the operand are clamped to in-range addresses.
+//
+// Every stage reads the same places relative to its first k, so each lane's
+// 32-bit offset of each block is computed once and a stage costs one scalar
+// base per operand and one move per block.  Recomputed per stage (64-bit
+// row * ld + k with clamps, 15 to 25 vector instructions a block) the
+// addresses competed with the MFMAs for issue slots and, in the grouped
+// kernel, for registers: 512 BF16 members 651 -> 441 us, BF16 4096^3 with its
+// conversion 174 -> 164 us, FP32 4096^3 NN 1080 -> 1017 us.  The last, partial
+// stage moves the offsets beyond K back to the last chunk or row; operands
+// whose tile spans 2^31 bytes or more (ld >= 2^31 / (tile rows * EB): the
+// offsets would not hold) compute whole addresses.
+template <typename Cfg, int EB, int BM, int BN, int BK, int TA, int TB, typename Swz>
+struct DmaSource {
+  static constexpr int CE = 16 / EB;   // elements per chunk
+  uint32_t off[Cfg::NW_HI];
+  const char* a;                       // first element of the tile at the next stage's first k
+  const char* b;
+  int64_t step_a, step_b;              // bytes per stage
+  int wave, lane;
+  int whole;                           // whole stages left to issue
+  int tail;                            // K positions of the stage after them
+  bool offsets;                        // the 32-bit offsets hold
+
+  // Chunk of block q this lane moves: tile row (K-major) or k (M/N-major)
+  // and element column.
+  __device__ __forceinline__ static void place(int q, int lane, bool& is_a, bool& kmajor, int& r,
+                                               int& col) {
+    is_a = q < Cfg::NBA;
+    const int o = (is_a ? q : q - Cfg::NBA) * 1024 + lane * 16;   // byte in the operand's tile
+    kmajor = is_a ? (TA == 0) : (TB == 1);
     if (kmajor) {
-      constexpr int ROWB = BK * EB, CPR = ROWB / 16;
-      const int r = o / ROWB, p = (o % ROWB) / 16;
-      const int c = p ^ kswz<CPR>(r);
-      int64_t row = c0 + r;
-      row = row < lim ? row : lim - 1;
-      int64_t kk = k0 + (int64_t)c * CE;
-      kk = kk < args.K ? kk : ((args.K - 1) / CE) * CE;   // chunks beyond K: the last one
-      elem = row * ld + kk;
+      constexpr int ROWB = BK * EB;
+      r = o / ROWB;
+      col = (((o % ROWB) / 16) ^ Swz::k(r)) * CE;
     } else {
-      const int ROWB = rows_c * EB, CPR = ROWB / 16;
-      const int k = o / ROWB, p = (o % ROWB) / 16;
-      const int W = EB == 2 ? 4 : 2;
-      const int RP = CPR >= 16 ? 1 : 16 / CPR;
-      const int c = p ^ (((k / RP) * W) % CPR);
-      int64_t kr = k0 + k;
-      kr = kr < args.K ? kr : args.K - 1;
-      int64_t col = c0 + (int64_t)c * CE;
-      col = col < lim ? col : ((lim - 1) / CE) * CE;      // chunks beyond the extent: the last
-      elem = kr * ld + col;
+      const int rowb = (is_a ? BM : BN) * EB;
+      r = o / rowb;
+      col = (((o % rowb) / 16) ^ (is_a ? Swz::mn_a(r) : Swz::mn_b(r))) * CE;
     }
-    char* dst = stage + (isA ? 0 : Cfg::A_BYTES) + blk * 1024;
-    lds_dma16(base + elem * EB, dst);
   }
-}
+
+  // Whether block i of every wave exists, and whether it is one of A's for
+  // every wave / for none; only where the blocks do not divide evenly is
+  // either asked of the wave.
+  __device__ __forceinline__ bool exists(int i) const {
+    return (i + 1) * Cfg::WAVES <= Cfg::NBLK || wave + i * Cfg::WAVES < Cfg::NBLK;
+  }
+  __device__ __forceinline__ bool of_a(int i) const {
+    if ((i + 1) * Cfg::WAVES <= Cfg::NBA) return true;
+    return i * Cfg::WAVES < Cfg::NBA && wave + i * Cfg::WAVES < Cfg::NBA;
+  }
+
+  // Offsets of block i beyond K in the last stage, moved back to its last
+  // chunk or row.
+  __device__ __forceinline__ uint32_t in_tail(const GemmArgs& g, int i) const {
+    bool is_a, kmajor;
+    int r, col;
+    place(wave + i * Cfg::WAVES, lane, is_a, kmajor, r, col);
+    if (kmajor) return off[i] - (uint32_t)max(col - (tail - 1) / CE * CE, 0) * EB;
+    return off[i] - (uint32_t)max(r - (tail - 1), 0) * (uint32_t)((is_a ? g.lda : g.ldb) * EB);
+  }
+
+  __device__ __forceinline__ void init(const GemmArgs& g, const char* Ag, const char* Bg,
+                                       int64_t m0, int64_t n0, int wave_, int lane_) {
+    wave = wave_;
+    lane = lane_;
+    a = uniform_ptr(Ag + m0 * (TA == 0 ? g.lda : 1) * EB);
+    b = uniform_ptr(Bg + n0 * (TB == 1 ? g.ldb : 1) * EB);
+    step_a = (int64_t)BK * (TA == 0 ? 1 : g.lda) * EB;
+    step_b = (int64_t)BK * (TB == 1 ? 1 : g.ldb) * EB;
+    whole = (int)((uint64_t)g.K / BK);
+    tail = (int)((uint64_t)g.K % BK);
+    // tile rows times ld below 2^31 bytes (shifts: compares of 64-bit values
+    // leave the scalar unit)
+    constexpr int LOG_A = 31 - __builtin_ctz((TA == 0 ? BM : BK) * EB);
+    constexpr int LOG_B = 31 - __builtin_ctz((TB == 1 ? BN : BK) * EB);
+    offsets = (((uint64_t)g.lda >> LOG_A) | ((uint64_t)g.ldb >> LOG_B)) == 0;
+    const uint64_t over_m = (uint64_t)(g.M - m0), over_n = (uint64_t)(g.N - n0);
+    const int left_m = (over_m >> 31) ? BM : min(BM, (int)over_m);
+    const int left_n = (over_n >> 31) ? BN : min(BN, (int)over_n);
+#pragma unroll
+    for (int i = 0; i < Cfg::NW_HI; ++i) {
+      bool is_a, kmajor;
+      int r, col;
+      place(exists(i) ? wave + i * Cfg::WAVES : 0, lane, is_a, kmajor, r, col);
+      const int left = is_a ? left_m : left_n;   // rows or columns
+      const uint32_t ld = (uint32_t)(is_a ? g.lda : g.ldb);
+      if (kmajor) r = min(r, left - 1);
+      else col = min(col, (int)((uint32_t)(left - 1) / CE * CE));
+      off[i] = ((uint32_t)r * ld + (uint32_t)col) * EB;
+    }
+  }
+
+  // Issue the next stage into the LDS at byte address `stage`.
+  __device__ __forceinline__ void issue(const GemmArgs& g, int64_t m0, int64_t n0, uint32_t stage) {
+    if (offsets) {
+      if (whole > 0) {
+#pragma unroll
+        for (int i = 0; i < Cfg::NW_HI; ++i)
+          if (exists(i))
+            lds_dma16(of_a(i) ? a : b, off[i], stage + (wave + i * Cfg::WAVES) * 1024);
+      } else {
+#pragma unroll
+        for (int i = 0; i < Cfg::NW_HI; ++i)
+          if (exists(i))
+            lds_dma16(of_a(i) ? a : b, in_tail(g, i), stage + (wave + i * Cfg::WAVES) * 1024);
+      }
+    } else {
+      // whole addresses: a loop, out of the way of the products that have offsets
+      const int left_k = whole > 0 ? BK : tail;
+#pragma nounroll
+      for (int q = wave; q < Cfg::NBLK; q += Cfg::WAVES) {
+        bool is_a, kmajor;
+        int r, col;
+        place(q, lane, is_a, kmajor, r, col);
+        const int64_t left = is_a ? g.M - m0 : g.N - n0;
+        const int64_t ld = is_a ? g.lda : g.ldb;
+        int64_t row = r, c = col;
+        if (kmajor) {
+          row = min(row, left - 1);
+          c = min(col, (left_k - 1) / CE * CE);       // chunks beyond K: the last one
+        } else {
+          row = min(r, left_k - 1);
+          c = min(c, (left - 1) / CE * CE);           // chunks beyond the extent: the last one
+        }
+        lds_dma16((is_a ? a : b) + (row * ld + c) * EB, stage + q * 1024);
+      }
+    }
+    a += step_a;
+    b += step_b;
+    --whole;
+  }
+};
+
+template <int EB, int BM, int BN, int BK>
+struct LpSwz {
+  __device__ __forceinline__ static int k(int r) { return kswz<BK * EB / 16>(r); }
+  __device__ __forceinline__ static int mn_a(int r) { return mswz<BM * EB / 16, EB == 2 ? 4 : 2>(r); }
+  __device__ __forceinline__ static int mn_b(int r) { return mswz<BN * EB / 16, EB == 2 ? 4 : 2>(r); }
+};
 
 // Zero K positions kvalid .. BK-1 of a stage (the last, partial one).
 template <int EB, int BM, int BN, int T, int BK, int TA, int TB>
 __device__ __forceinline__ void lp_dma_zero_tail(char* stage, int kvalid, int tid) {
   using Cfg = LpDmaCfg<EB, BM, BN, T, BK, TA, TB>;
   typedef typename LpElem<EB>::T E;
+  asm volatile("" : "+s"(kvalid));   // keeps this rarely run arithmetic out of the stage loop's preheader
 #pragma unroll
   for (int op = 0; op < 2; ++op) {
     const bool kmajor = op == 0 ? (TA == 0) : (TB == 1);
@@ -263,13 +384,15 @@ __device__ __forceinline__ void lp_dma_tile(const GemmArgs& args, int tm, int tn
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
-  const int wave = tid >> 6;
+  const int wave = Cfg::WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t lds0 = lds_address(lds);
   const int wm0 = (wave / Base::WAVES_N) * WT;
   const int wn0 = (wave % Base::WAVES_N) * WT;
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
   const int64_t M = args.M, N = args.N, K = args.K;
-  const char* __restrict__ Ag = static_cast<const char*>(args.A) + bz * args.sA * EB;
-  const char* __restrict__ Bg = static_cast<const char*>(args.B) + bz * args.sB * EB;
+  DmaSource<Cfg, EB, BM, BN, BK, TA, TB, LpSwz<EB, BM, BN, BK>> src;
+  src.init(args, static_cast<const char*>(args.A) + bz * args.sA * EB,
+           static_cast<const char*>(args.B) + bz * args.sB * EB, m0, n0, wave, lane);
   float scale = args.alpha;
   if (EB == 1) scale = args.alpha / (args.scaleA[0] * args.scaleB[0]);
 
@@ -290,11 +413,9 @@ __device__ __forceinline__ void lp_dma_tile(const GemmArgs& args, int tm, int tn
   const int my_blocks = (wave < Cfg::NBLK % Cfg::WAVES || Cfg::NBLK % Cfg::WAVES == 0)
                             ? Cfg::NW_HI : Cfg::NW_LO;
 
-#pragma unroll
+#pragma nounroll
   for (int s = 0; s < NS - 1; ++s)
-    if (s < nk)
-      lp_dma_issue<EB, BM, BN, T, BK, TA, TB>(args, Ag, Bg, m0, n0, (int64_t)s * BK,
-                                              lds + s * Cfg::STAGE, wave, lane);
+    if (s < nk) src.issue(args, m0, n0, lds0 + s * Cfg::STAGE);
 
   for (int kt = 0; kt < nk; ++kt) {
     // stage kt has landed once at most `ahead` later stages are in flight
@@ -308,8 +429,7 @@ __device__ __forceinline__ void lp_dma_tile(const GemmArgs& args, int tm, int tn
     }
     // the buffer of stage kt - 1 is free: every wave has passed its reads
     if (kt + NS - 1 < nk)
-      lp_dma_issue<EB, BM, BN, T, BK, TA, TB>(args, Ag, Bg, m0, n0, (int64_t)(kt + NS - 1) * BK,
-                                              lds + ((kt + NS - 1) % NS) * Cfg::STAGE, wave, lane);
+      src.issue(args, m0, n0, lds0 + ((kt + NS - 1) % NS) * Cfg::STAGE);
     const char* at = cur;
     const char* bt = cur + Cfg::A_BYTES;
 #pragma unroll
@@ -357,7 +477,8 @@ gemm_lp_dma_kernel(GemmArgs args) {
   __shared__ __attribute__((aligned(16))) char lds[Cfg::LDS_BYTES];
   int tm, tn;
   int64_t bz;
-  block_coords(blockIdx.x, args.tiles_m, args.tiles_n, args.batch, tm, tn, bz);
+  load_args(args);
+  block_coords(blockIdx.x, args, tm, tn, bz);
   lp_dma_tile<EB, BM, BN, T, BK, TA, TB>(args, tm, tn, bz, lds);
 }
 

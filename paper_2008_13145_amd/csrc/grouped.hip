@@ -104,7 +104,7 @@ grouped_bf16_kernel(const GroupDesc* __restrict__ descs, const WorkItem* __restr
     if (dynamic) {
       if (threadIdx.x == 0) s_w = (int32_t)atomicAdd(counter, 1u);
       __syncthreads();
-      w = s_w;
+      w = __builtin_amdgcn_readfirstlane(s_w);   // scalar: item and member by scalar loads
     }
     if (w >= n_work) break;
     const WorkItem it = work[w];
