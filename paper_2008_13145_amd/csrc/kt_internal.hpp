@@ -24,6 +24,7 @@ struct Tree {
 struct MlpModel {
   int32_t k = 0;
   std::vector<float> params;   // W1 b1 W2 b2 W3 b3 packed
+  std::vector<float> packed;   // the same input-major for the host's vector forward pass
 };
 
 struct ShapeKey {

@@ -20,6 +20,10 @@
 #include <algorithm>
 #include <vector>
 
+#if !defined(__HIP_DEVICE_COMPILE__) && defined(__x86_64__)
+#include <immintrin.h>
+#endif
+
 #include "kt_internal.hpp"
 
 namespace kt {
@@ -371,8 +375,72 @@ static void he_uniform(std::vector<float>& P, int k, uint64_t seed) {
   fill(L.oW3, k, MLP_H);
 }
 
+// Host weights input-major, outputs padded to whole vectors of 8: W1 [6][64],
+// b1, W2 [64][64], b2, W3 [64][kp], b3 [kp] with kp = k rounded up to 8.
+static void mlp_pack_host(MlpModel& m) {
+  m.packed.clear();
+  if (m.k < 1 || m.k > MLP_MAX_K) return;   // a loaded model may be larger: the plain pass takes it
+  const MlpLayout L(m.k);
+  const int kp = (m.k + 7) / 8 * 8;
+  m.packed.assign(MLP_IN * MLP_H + MLP_H + MLP_H * MLP_H + MLP_H + MLP_H * kp + kp, 0.f);
+  const float* P = m.params.data();
+  float* o = m.packed.data();
+  auto layer = [&](int w, int b, int n_in, int n_out, int stride) {
+    for (int i = 0; i < n_in; ++i)
+      for (int j = 0; j < n_out; ++j) o[i * stride + j] = P[w + j * n_in + i];
+    for (int j = 0; j < n_out; ++j) o[n_in * stride + j] = P[b + j];
+    o += (n_in + 1) * stride;
+  };
+  layer(L.oW1, L.ob1, MLP_IN, MLP_H, MLP_H);
+  layer(L.oW2, L.ob2, MLP_H, MLP_H, MLP_H);
+  layer(L.oW3, L.ob3, MLP_H, m.k, kp);
+}
+
+#if !defined(__HIP_DEVICE_COMPILE__) && defined(__x86_64__)
+// mlp_forward_argmax with eight outputs of a layer in a vector: each output
+// is the same chain of fused multiply-adds over the inputs in the same order,
+// hence the same bits and the same pick as the device's.
+__attribute__((target("avx2,fma"))) static int mlp_forward_argmax_avx2(const kt_shape& shape,
+                                                                       const float* W, int k) {
+  alignas(32) float x[MLP_IN], h1[MLP_H], h2[MLP_H], y[MLP_MAX_K];
+  shape_features(shape, x);
+  const float* w = W;
+  const float* in = x;
+  const int kp = (k + 7) / 8 * 8;
+  const int n_in[3] = {MLP_IN, MLP_H, MLP_H}, n_out[3] = {MLP_H, MLP_H, kp};
+  float* outs[3] = {h1, h2, y};
+  for (int l = 0; l < 3; ++l) {
+    const int n = n_in[l], m = n_out[l];
+    for (int j0 = 0; j0 < m; j0 += 32) {   // four chains at a time
+      const int nv = (m - j0) / 8 < 4 ? (m - j0) / 8 : 4;
+      __m256 acc[4];
+      for (int v = 0; v < nv; ++v) acc[v] = _mm256_loadu_ps(w + n * m + j0 + 8 * v);
+      for (int i = 0; i < n; ++i) {
+        const __m256 a = _mm256_set1_ps(in[i]);
+        for (int v = 0; v < nv; ++v)
+          acc[v] = _mm256_fmadd_ps(a, _mm256_loadu_ps(w + i * m + j0 + 8 * v), acc[v]);
+      }
+      for (int v = 0; v < nv; ++v)   // fmaxf(s, 0): max(s, 0) gives 0 for NaN as fmaxf does
+        _mm256_storeu_ps(outs[l] + j0 + 8 * v, l < 2 ? _mm256_max_ps(acc[v], _mm256_setzero_ps()) : acc[v]);
+    }
+    w += (n + 1) * m;
+    in = outs[l];
+  }
+  int best = 0;
+  for (int o = 1; o < k; ++o)
+    if (y[o] > y[best]) best = o;
+  return best;
+}
+
+static bool host_has_fma() {
+  static const bool v = __builtin_cpu_supports("avx2") && __builtin_cpu_supports("fma");
+  return v;
+}
+#endif
+
 kt_status mlp_upload(Ctx* h, int dtype) {
   SelState& S = h->sel[dtype];
+  mlp_pack_host(S.mlp);
   if (h->device < 0) return KT_OK;
   if (S.d_mlp) { (void)hipFree(S.d_mlp); S.d_mlp = nullptr; }
   const size_t pbytes = S.mlp.params.size() * 4, cbytes = S.chosen.size() * 4;
@@ -405,6 +473,14 @@ kt_status mlp_select_batch(Ctx* h, int dtype, const kt_shape* d_shapes, int32_t 
 kt_status mlp_select_host(Ctx* h, int dtype, const kt_shape* s, int32_t* id) {
   const SelState& S = h->sel[dtype];
   if (S.mlp.params.empty() || S.mlp.k < 1) return fail(h, KT_ENOTFITTED, "no MLP weights");
+#if !defined(__HIP_DEVICE_COMPILE__) && defined(__x86_64__)
+  // 4992 calls of the C library's fmaf took 6 us of every kt_gemm(-1) call,
+  // more than a small kernel; in vectors they take 0.3 us
+  if (host_has_fma() && !S.mlp.packed.empty()) {
+    *id = S.chosen[mlp_forward_argmax_avx2(*s, S.mlp.packed.data(), S.mlp.k)];
+    return KT_OK;
+  }
+#endif
   *id = S.chosen[mlp_forward_argmax(*s, S.mlp.params.data(), S.mlp.k)];
   return KT_OK;
 }

@@ -259,25 +259,38 @@ static kt_status time_candidates(Ctx* h, int dtype, const kt_shape* s,
   hipEvent_t e0, e1;
   if ((e = hipEventCreate(&e0)) != hipSuccess) return hip_fail(h, e, "event");
   if ((e = hipEventCreate(&e1)) != hipSuccess) { (void)hipEventDestroy(e0); return hip_fail(h, e, "event"); }
-  int32_t best = -1;
-  float best_ms = 0.f;
+  // Two rounds: all candidates, then again those within 1.5x of the fastest,
+  // each taken at its better time.  In one round the candidate that happens
+  // to run while the clock still settles loses by up to 15 % and is cached
+  // so (FP32 4096^3: 1150 us picked over 1017 us).
+  constexpr float AGAIN = 1.5f;
+  std::vector<float> t(cands.size(), -1.f);
   kt_status st = KT_OK;
-  for (size_t ci = 0; ci < cands.size() && st == KT_OK; ++ci) {
-    const int32_t id = cands[ci];
-    if (!find_launcher(h, dtype, kernel_base(h, dtype, id), s->transA, s->transB)) continue;
-    auto launch = [&]() {
-      return run_kernel(h, dtype, s, 1.f, A, lda, a_rows * lda, B, ldb, b_rows * ldb, 0.f, C, ldc,
-                        s->M * ldc, scales, scales + 1, id, base + offW, planes, nullptr);
-    };
-    if ((st = launch()) != KT_OK) break;
-    (void)hipEventRecord(e0, nullptr);
-    for (int r = 0; r < 3 && st == KT_OK; ++r) st = launch();
-    (void)hipEventRecord(e1, nullptr);
-    if ((e = hipEventSynchronize(e1)) != hipSuccess) { st = hip_fail(h, e, "sync"); break; }
-    float ms = 0.f;
-    (void)hipEventElapsedTime(&ms, e0, e1);
-    if (best < 0 || ms < best_ms) { best = id; best_ms = ms; }
+  float best_ms = -1.f;
+  for (int round = 0; round < 2 && st == KT_OK; ++round) {
+    const float limit = best_ms * AGAIN;
+    for (size_t ci = 0; ci < cands.size() && st == KT_OK; ++ci) {
+      const int32_t id = cands[ci];
+      if (!find_launcher(h, dtype, kernel_base(h, dtype, id), s->transA, s->transB)) continue;
+      if (round == 1 && t[ci] > limit) continue;
+      auto launch = [&]() {
+        return run_kernel(h, dtype, s, 1.f, A, lda, a_rows * lda, B, ldb, b_rows * ldb, 0.f, C, ldc,
+                          s->M * ldc, scales, scales + 1, id, base + offW, planes, nullptr);
+      };
+      if ((st = launch()) != KT_OK) break;
+      (void)hipEventRecord(e0, nullptr);
+      for (int r = 0; r < 3 && st == KT_OK; ++r) st = launch();
+      (void)hipEventRecord(e1, nullptr);
+      if ((e = hipEventSynchronize(e1)) != hipSuccess) { st = hip_fail(h, e, "sync"); break; }
+      float ms = 0.f;
+      (void)hipEventElapsedTime(&ms, e0, e1);
+      if (t[ci] < 0.f || ms < t[ci]) t[ci] = ms;
+      if (best_ms < 0.f || ms < best_ms) best_ms = ms;
+    }
   }
+  int32_t best = -1;
+  for (size_t ci = 0; ci < cands.size(); ++ci)
+    if (t[ci] >= 0.f && t[ci] == best_ms && best < 0) best = cands[ci];
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (st != KT_OK) return st;
