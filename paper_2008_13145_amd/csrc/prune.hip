@@ -77,7 +77,7 @@ const std::vector<uint16_t>& sigmoid_table(Ctx* h) {
 
 static constexpr int KM_THREADS = 1024;
 static constexpr int KM_MAX_ROWS = 4096;
-static constexpr int KM_MAX_KD = 8192;      // k * d int64 centroids in LDS
+static constexpr int KM_MAX_KD = 8192;      // k * d member sums in LDS
 
 struct KmeansOut {      // per restart, in the workspace
   int64_t inertia;
@@ -131,38 +131,161 @@ __device__ int64_t block_sum(int64_t v, int64_t* s_val) {
   return r;
 }
 
-// Squared distance between row i of X and centroid c (int64 values).
-__device__ __forceinline__ int64_t sqdist_row(const uint16_t* __restrict__ X, int d, int i,
-                                              const int64_t* c) {
-  const uint16_t* x = X + (int64_t)i * d;
-  int64_t s = 0;
-  for (int f = 0; f < d; ++f) {
-    const int64_t df = (int64_t)x[f] - c[f];
-    s += df * df;
+// The clustering works on the INT8 matrix cores.  A 16-bit value is
+// x = 256 (a + 128) + (b + 128) with signed bytes a, b, and the offset cancels
+// in x - c, so with x' = 256 a + b
+//   |x - c|^2 = sum x'^2 - 2 sum x' c' + sum c'^2,
+//   x' c' = 65536 a_x a_c + 256 (a_x b_c + b_x a_c) + b_x b_c:
+// four byte products, each an exact 32-bit sum of a 16x16x64 INT8 MFMA (at
+// most 8192 terms of 2^14).  The 16 columns of one MFMA are the two bytes of
+// eight centroids, its rows sixteen rows of X, once for each byte of X.
+struct KmLayout {          // LDS of one restart, in bytes
+  int kt;                  // column tiles: eight centroids each
+  int dp;                  // dimensions in whole 64-deep steps
+  int o_planes, o_sums, o_xx, o_dist, o_cc, o_val, o_labels, o_counts, o_idx, total;
+  __host__ __device__ KmLayout(int n, int d, int k) {
+    kt = (k + 7) / 8;
+    dp = (d + 63) / 64 * 64;
+    int o = 0;
+    auto take = [&](int bytes) { const int at = o; o += (bytes + 15) / 16 * 16; return at; };
+    o_planes = take(2 * k * dp);        // centroid bytes [column][dp]
+    o_sums = take(k * d * 4);           // member sums, at most 4096 * 65535
+    o_xx = take(n * 8);                 // sum x'^2 per row
+    o_dist = take(n * 8);
+    o_cc = take(kt * 8 * 8);            // sum c'^2 per centroid
+    o_val = take(KM_THREADS * 8);
+    o_labels = take(n);
+    o_counts = take(k * 4);
+    o_idx = take(KM_THREADS * 4);
+    total = o;
   }
-  return s;
+};
+
+typedef int i32x4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4h __attribute__((ext_vector_type(4), aligned(2)));
+
+// One lane's bytes of 16 consecutive values of row i from column c0: the
+// high bytes in hi, the low ones in lo, both signed; zero beyond d.
+__device__ __forceinline__ void km_load(const uint16_t* __restrict__ X, int d, int i, int c0,
+                                        i32x4v& hi, i32x4v& lo) {
+  const uint16_t* p = X + (int64_t)i * d + c0;
+  uint32_t w[8];
+  uint32_t keep[4];
+  if (c0 + 16 <= d) {
+    const u32x4h u = *reinterpret_cast<const u32x4h*>(p);
+    const u32x4h v = *reinterpret_cast<const u32x4h*>(p + 8);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) { w[q] = u[q]; w[4 + q] = v[q]; keep[q] = 0xffffffffu; }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const uint32_t e0 = c0 + 2 * q < d ? p[2 * q] : 0u, e1 = c0 + 2 * q + 1 < d ? p[2 * q + 1] : 0u;
+      w[q] = e0 | (e1 << 16);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int left = d - c0 - 4 * q;
+      keep[q] = left >= 4 ? 0xffffffffu : left <= 0 ? 0u : (1u << (8 * left)) - 1u;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    hi[q] = (int)((__builtin_amdgcn_perm(w[2 * q + 1], w[2 * q], 0x07050301u) ^ 0x80808080u) & keep[q]);
+    lo[q] = (int)((__builtin_amdgcn_perm(w[2 * q + 1], w[2 * q], 0x06040200u) ^ 0x80808080u) & keep[q]);
+  }
+}
+
+// Dot products of 16 rows (tile t) with the eight centroids of column tile ct:
+// in lane l, x'_row . c'_j for rows 4 (l / 16) + r, r = 0..3, and centroid
+// j = 8 ct + (l % 16) / 2 (both lanes of a pair hold it).
+__device__ __forceinline__ void km_dots(const uint16_t* __restrict__ X, int n, int d, int t, int ct,
+                                        const char* planes, int dp, int k, int lane, int64_t dot[4]) {
+  const int row = min(t * 16 + (lane & 15), n - 1), kg = (lane >> 4) * 16;
+  i32x4v ah = {0, 0, 0, 0}, al = {0, 0, 0, 0};
+  const char* bp = planes + min(ct * 16 + (lane & 15), 2 * k - 1) * dp + kg;   // spare columns: any
+  for (int s = 0; s < dp; s += 64) {
+    i32x4v hi, lo;
+    km_load(X, d, row, s + kg, hi, lo);
+    const i32x4v b = *reinterpret_cast<const i32x4v*>(bp + s);
+    ah = __builtin_amdgcn_mfma_i32_16x16x64_i8(hi, b, ah, 0, 0, 0);
+    al = __builtin_amdgcn_mfma_i32_16x16x64_i8(lo, b, al, 0, 0, 0);
+  }
+  const int sh = (lane & 1) ? 0 : 8;   // even columns hold the centroids' high bytes
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    const int64_t v = ((int64_t)ah[r] * 256 + al[r]) << sh;
+    dot[r] = v + __shfl_xor(v, 1);
+  }
+}
+
+// Write centroid j (one value per dimension) as bytes and its sum c'^2, by
+// one wave; value(f) gives dimension f.
+template <typename F>
+__device__ __forceinline__ void km_set_centroid(char* planes, int64_t* cc, int dp, int d, int j,
+                                                int lane, F value) {
+  int64_t q = 0;
+  for (int f = lane; f < d; f += 64) {
+    const uint32_t v = value(f);
+    planes[(2 * j) * dp + f] = (char)((v >> 8) ^ 0x80u);
+    planes[(2 * j + 1) * dp + f] = (char)((v & 0xffu) ^ 0x80u);
+    const int64_t c = (int64_t)v - 32896;
+    q += c * c;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+  if (lane == 0) cc[j] = q;
 }
 
 // One restart per work-group.  Outputs in global memory: centroids
 // [restart][k][d], labels [restart][n], KmeansOut [restart].
+//
+// An iteration reads X once from L2 (960 x 188: 361 KB, about 2.6 us at one
+// CU's 64 B a clock), which bounds it; the products are 360 MFMAs.  Rows that
+// change their cluster move between the member sums as they are found, so the
+// update costs the changed rows only (the sums are exact integers).  With 64-bit
+// vector arithmetic and a serial pass over the rows per dimension the same ten
+// restarts of 960 x 188, k = 8, took 32 ms.
 __global__ void __launch_bounds__(KM_THREADS)
 kmeans_kernel(const uint16_t* __restrict__ X, int n, int d, int k, uint64_t seed, int max_iter,
               int64_t* __restrict__ g_cent, int32_t* __restrict__ g_labels,
               KmeansOut* __restrict__ g_out) {
-  extern __shared__ int64_t smem[];
-  int64_t* C = smem;                                  // [k][d]
-  int64_t* dist = C + (int64_t)k * d;                 // [n]
-  int64_t* s_val = dist + n;                          // [KM_THREADS]
-  int32_t* labels = (int32_t*)(s_val + KM_THREADS);   // [n]
-  int32_t* counts = labels + n;                       // [k]
-  int32_t* s_idx = counts + k;                        // [KM_THREADS]
+  extern __shared__ __attribute__((aligned(16))) char km_lds[];
+  const KmLayout L(n, d, k);
+  char* planes = km_lds + L.o_planes;
+  uint32_t* sums = (uint32_t*)(km_lds + L.o_sums);
+  int64_t* xx = (int64_t*)(km_lds + L.o_xx);
+  int64_t* dist = (int64_t*)(km_lds + L.o_dist);
+  int64_t* cc = (int64_t*)(km_lds + L.o_cc);
+  int64_t* s_val = (int64_t*)(km_lds + L.o_val);
+  uint8_t* labels = (uint8_t*)(km_lds + L.o_labels);
+  int32_t* counts = (int32_t*)(km_lds + L.o_counts);
+  int32_t* s_idx = (int32_t*)(km_lds + L.o_idx);
   __shared__ int32_t s_flag;
   __shared__ int32_t s_pick;
+  __shared__ int64_t s_target;
   __shared__ int32_t s_centres[64];
+  constexpr uint8_t NO_LABEL = 255;   // k <= 64
+  constexpr int WAVES = KM_THREADS / 64;
 
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = blockIdx.x;
+  const int tiles = (n + 15) / 16;
   uint64_t state = seed + (uint64_t)r;   // thread 0 owns the stream
+
+  for (int e = tid; e < 2 * k * L.dp / 4; e += KM_THREADS) ((uint32_t*)planes)[e] = 0u;
+  for (int e = tid; e < k * d; e += KM_THREADS) sums[e] = 0u;
+  for (int j = tid; j < k; j += KM_THREADS) counts[j] = 0;
+  for (int i = tid; i < n; i += KM_THREADS) { labels[i] = NO_LABEL; dist[i] = INT64_MAX; }
+  for (int i = wave; i < n; i += WAVES) {
+    int64_t q = 0;
+    for (int f = lane; f < d; f += 64) {
+      const int64_t v = (int64_t)X[(int64_t)i * d + f] - 32896;
+      q += v * v;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) q += __shfl_xor(q, o);
+    if (lane == 0) xx[i] = q;
+  }
 
   // ---- k-means++ initialisation
   if (tid == 0) {
@@ -171,92 +294,149 @@ kmeans_kernel(const uint16_t* __restrict__ X, int n, int d, int k, uint64_t seed
     s_centres[0] = s_pick;
   }
   __syncthreads();
-  for (int f = tid; f < d; f += KM_THREADS) C[f] = X[(int64_t)s_pick * d + f];
-  __syncthreads();
-  for (int i = tid; i < n; i += KM_THREADS) dist[i] = sqdist_row(X, d, i, C);
-  __syncthreads();
-  for (int c = 1; c < k; ++c) {
-    // Prefix search: each thread owns a contiguous chunk of rows.
-    const int chunk = (n + KM_THREADS - 1) / KM_THREADS;
-    const int lo = tid * chunk, hi = min(n, lo + chunk);
-    int64_t part = 0;
-    for (int i = lo; i < hi; ++i) part += dist[i];
-    s_val[tid] = part;
-    __syncthreads();
-    if (tid == 0) {
-      int64_t S = 0;
-      for (int t = 0; t < KM_THREADS; ++t) S += s_val[t];
-      const uint64_t draw = sm64_next(state);
-      int pick = -1;
-      if (S == 0) {
-        for (int i = 0; i < n && pick < 0; ++i) {
-          bool used = false;
-          for (int j = 0; j < c; ++j) used = used || (s_centres[j] == i);
-          if (!used) pick = i;
-        }
-      } else {
-        const int64_t rr = (int64_t)(draw % (uint64_t)S);
-        int64_t run = 0;
-        int t = 0;
-        while (t < KM_THREADS && run + s_val[t] <= rr) { run += s_val[t]; ++t; }
-        for (int i = t * chunk; i < n; ++i) {
-          run += dist[i];
-          if (run > rr) { pick = i; break; }
+  for (int c = 0; c < k; ++c) {
+    if (c > 0) {
+      // each thread owns a contiguous chunk of rows; exclusive prefix sums of
+      // the chunks place the draw
+      const int chunk = (n + KM_THREADS - 1) / KM_THREADS;
+      const int lo = min(n, tid * chunk), hi = min(n, lo + chunk);
+      int64_t part = 0;
+      for (int i = lo; i < hi; ++i) part += dist[i];
+      int64_t run = part;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int64_t up = __shfl_up(run, o);
+        if (lane >= o) run += up;
+      }
+      if (lane == 63) s_val[wave] = run;
+      __syncthreads();
+      int64_t before = 0, S = 0;
+      for (int w = 0; w < WAVES; ++w) {
+        if (w < wave) before += s_val[w];
+        S += s_val[w];
+      }
+      if (tid == 0) {
+        const uint64_t draw = sm64_next(state);
+        s_target = S == 0 ? -1 : (int64_t)(draw % (uint64_t)S);
+        s_pick = 0;
+        if (S == 0) {   // every row coincides with a centre: the first unused row
+          int pick = -1;
+          for (int i = 0; i < n && pick < 0; ++i) {
+            bool used = false;
+            for (int j = 0; j < c; ++j) used = used || (s_centres[j] == i);
+            if (!used) pick = i;
+          }
+          s_pick = pick < 0 ? 0 : pick;
         }
       }
-      if (pick < 0) pick = 0;   // unreachable for 1 <= k <= n; keeps the index in range
-      s_pick = pick;
-      s_centres[c] = pick;
+      __syncthreads();
+      const int64_t rr = s_target;
+      const int64_t start = before + run - part;
+      if (rr >= start && rr < start + part) {   // one thread: the chunks do not overlap
+        int64_t acc = start;
+        for (int i = lo; i < hi; ++i) {
+          acc += dist[i];
+          if (acc > rr) { s_pick = i; break; }
+        }
+      }
+      __syncthreads();
+      if (tid == 0) s_centres[c] = s_pick;
     }
+    const int64_t pick = s_pick;
+    if (wave == 0)
+      km_set_centroid(planes, cc, L.dp, d, c, lane, [&](int f) { return (uint32_t)X[pick * d + f]; });
     __syncthreads();
-    int64_t* Cc = C + (int64_t)c * d;
-    for (int f = tid; f < d; f += KM_THREADS) Cc[f] = X[(int64_t)s_pick * d + f];
-    __syncthreads();
-    for (int i = tid; i < n; i += KM_THREADS) {
-      const int64_t v = sqdist_row(X, d, i, Cc);
-      if (v < dist[i]) dist[i] = v;
+    const int64_t ccj = cc[c];
+    for (int t = wave; t < tiles; t += WAVES) {
+      int64_t dot[4];
+      km_dots(X, n, d, t, c / 8, planes, L.dp, k, lane, dot);
+      if ((lane & 15) == 2 * (c % 8)) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int i = t * 16 + (lane >> 4) * 4 + q;
+          if (i < n) {
+            const int64_t v = xx[i] + ccj - 2 * dot[q];
+            if (v < dist[i]) dist[i] = v;
+          }
+        }
+      }
     }
     __syncthreads();
   }
 
   // ---- Lloyd iterations
-  for (int i = tid; i < n; i += KM_THREADS) labels[i] = -1;
-  __syncthreads();
   int it = 0;
-  bool converged = false;
   for (;;) {
     // assignment: nearest centroid, lowest index on ties
     if (tid == 0) s_flag = 0;
     __syncthreads();
-    int changed = 0;
-    for (int i = tid; i < n; i += KM_THREADS) {
-      int64_t bd = INT64_MAX;
-      int bj = 0;
-      for (int j = 0; j < k; ++j) {
-        const int64_t v = sqdist_row(X, d, i, C + (int64_t)j * d);
-        if (v < bd) { bd = v; bj = j; }
+    bool changed = false;
+    for (int t = wave; t < tiles; t += WAVES) {
+      int64_t best[4];
+      int bj[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) { best[q] = INT64_MAX; bj[q] = 0; }
+      for (int ct = 0; ct < L.kt; ++ct) {
+        int64_t dot[4];
+        km_dots(X, n, d, t, ct, planes, L.dp, k, lane, dot);
+        const int j = ct * 8 + (lane & 15) / 2;
+        const int64_t ccj = j < k ? cc[j] : 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int64_t v = ccj - 2 * dot[q];
+          if (j < k && v < best[q]) { best[q] = v; bj[q] = j; }
+        }
       }
-      dist[i] = bd;
-      if (labels[i] != bj) changed = 1;
-      labels[i] = bj;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int o = 2; o < 16; o <<= 1) {
+          const int64_t ov = __shfl_xor(best[q], o);
+          const int oj = __shfl_xor(bj[q], o);
+          if (ov < best[q] || (ov == best[q] && oj < bj[q])) { best[q] = ov; bj[q] = oj; }
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = t * 16 + (lane >> 4) * 4 + q;
+        const bool in = i < n;
+        const int old = in ? labels[i] : 0;
+        const bool moved = in && old != bj[q];
+        if (in && (lane & 15) == 0) {
+          dist[i] = best[q] + xx[i];
+          if (moved) {
+            labels[i] = (uint8_t)bj[q];
+            atomicAdd(&counts[bj[q]], 1);
+            if (old != NO_LABEL) atomicSub(&counts[old], 1);
+          }
+        }
+        changed = changed || moved;
+        // the rows that moved, one of each 16-lane group, by the whole wave
+        uint64_t todo = __ballot(moved && (lane & 15) == 0);
+        while (todo) {
+          const int src = __ffsll((unsigned long long)todo) - 1;
+          todo &= todo - 1;
+          const int row = t * 16 + (src >> 4) * 4 + q;
+          const int to = __shfl(bj[q], src), from = __shfl(old, src);
+          for (int f = lane; f < d; f += 64) {
+            const uint32_t v = X[(int64_t)row * d + f];
+            atomicAdd(&sums[to * d + f], v);
+            if (from != NO_LABEL) atomicSub(&sums[from * d + f], v);
+          }
+        }
+      }
     }
     if (changed) atomicOr(&s_flag, 1);
     __syncthreads();
-    if (s_flag == 0 && it > 0) { converged = true; break; }
+    if (s_flag == 0 && it > 0) break;
     if (it >= max_iter) break;   // labels/dist already reflect the final centroids
-    // update: per-dimension sums into C (C is not needed after the assignment)
-    for (int j = tid; j < k; j += KM_THREADS) counts[j] = 0;
-    __syncthreads();
-    for (int i = tid; i < n; i += KM_THREADS) atomicAdd(&counts[labels[i]], 1);
-    for (int64_t e = tid; e < (int64_t)k * d; e += KM_THREADS) C[e] = 0;
-    __syncthreads();
-    for (int f = tid; f < d; f += KM_THREADS) {
-      for (int i = 0; i < n; ++i) C[(int64_t)labels[i] * d + f] += X[(int64_t)i * d + f];
-    }
-    __syncthreads();
-    for (int64_t e = tid; e < (int64_t)k * d; e += KM_THREADS) {
-      const int64_t nj = counts[e / d];
-      if (nj > 0) C[e] = (2 * C[e] + nj) / (2 * nj);
+    // update: rounded means
+    for (int j = wave; j < k; j += WAVES) {
+      const uint64_t nj = counts[j];
+      if (nj > 0)
+        km_set_centroid(planes, cc, L.dp, d, j, lane, [&](int f) {
+          return (uint32_t)((2 * (uint64_t)sums[j * d + f] + nj) / (2 * nj));
+        });
     }
     __syncthreads();
     // empty clusters take the farthest row (lowest index on ties); its distance is zeroed
@@ -265,18 +445,23 @@ kmeans_kernel(const uint16_t* __restrict__ X, int n, int d, int k, uint64_t seed
       int64_t fv;
       int32_t fi;
       block_argmax(dist, n, s_val, s_idx, fv, fi);
-      for (int f = tid; f < d; f += KM_THREADS) C[(int64_t)j * d + f] = X[(int64_t)fi * d + f];
-      __syncthreads();
+      if (wave == 0)
+        km_set_centroid(planes, cc, L.dp, d, j, lane,
+                        [&](int f) { return (uint32_t)X[(int64_t)fi * d + f]; });
       if (tid == 0) dist[fi] = 0;
       __syncthreads();
     }
     ++it;
   }
-  (void)converged;
   int64_t part = 0;
   for (int i = tid; i < n; i += KM_THREADS) part += dist[i];
   const int64_t inertia = block_sum(part, s_val);
-  for (int64_t e = tid; e < (int64_t)k * d; e += KM_THREADS) g_cent[(int64_t)r * k * d + e] = C[e];
+  for (int e = tid; e < k * d; e += KM_THREADS) {
+    const int j = e / d, f = e - j * d;
+    const uint32_t hi = (uint8_t)planes[(2 * j) * L.dp + f] ^ 0x80u;
+    const uint32_t lo = (uint8_t)planes[(2 * j + 1) * L.dp + f] ^ 0x80u;
+    g_cent[(int64_t)r * k * d + e] = hi * 256 + lo;
+  }
   for (int i = tid; i < n; i += KM_THREADS) g_labels[(int64_t)r * n + i] = labels[i];
   if (tid == 0) {
     g_out[r].inertia = inertia;
@@ -287,24 +472,45 @@ kmeans_kernel(const uint16_t* __restrict__ X, int n, int d, int k, uint64_t seed
 // Pick the winning restart (lowest inertia, lowest restart on ties) and map
 // its centroids to k distinct configurations: centroid j takes its largest
 // coordinate (lowest configuration on ties) among those not yet chosen.
-__global__ void choose_kernel(const int64_t* __restrict__ g_cent, const KmeansOut* __restrict__ g_out,
-                              int n_init, int k, int d, int32_t* __restrict__ chosen,
-                              int32_t* __restrict__ best_restart) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  int br = 0;
-  for (int r = 1; r < n_init; ++r)
-    if (g_out[r].inertia < g_out[br].inertia) br = r;
-  *best_restart = br;
+__global__ void __launch_bounds__(64)
+choose_kernel(const int64_t* __restrict__ g_cent, const KmeansOut* __restrict__ g_out, int n_init,
+              int k, int d, int32_t* __restrict__ chosen, int32_t* __restrict__ best_restart) {
+  __shared__ int32_t s_chosen[64];
+  const int lane = threadIdx.x;
+  // lexicographic minimum / maximum over the wave, lowest index on ties
+  auto best_of = [&](int64_t v, int i) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+      const int64_t ov = __shfl_xor(v, o);
+      const int oi = __shfl_xor(i, o);
+      if (ov > v || (ov == v && oi < i)) { v = ov; i = oi; }
+    }
+    return i;
+  };
+  int64_t bv = INT64_MIN;
+  int bi = INT32_MAX;
+  for (int r = lane; r < n_init; r += 64) {
+    const int64_t v = -g_out[r].inertia;
+    if (v > bv) { bv = v; bi = r; }
+  }
+  const int br = best_of(bv, bi);
+  if (lane == 0) *best_restart = br;
   const int64_t* C = g_cent + (int64_t)br * k * d;
   for (int j = 0; j < k; ++j) {
-    int best = -1;
-    for (int f = 0; f < d; ++f) {
+    bv = -1;   // below every coordinate
+    bi = INT32_MAX;
+    for (int f = lane; f < d; f += 64) {
       bool used = false;
-      for (int q = 0; q < j; ++q) used = used || (chosen[q] == f);
-      if (used) continue;
-      if (best < 0 || C[(int64_t)j * d + f] > C[(int64_t)j * d + best]) best = f;
+      for (int q = 0; q < j; ++q) used = used || (s_chosen[q] == f);
+      const int64_t v = C[(int64_t)j * d + f];
+      if (!used && v > bv) { bv = v; bi = f; }
     }
-    chosen[j] = best;
+    const int best = best_of(bv, bi);
+    if (lane == 0) {
+      s_chosen[j] = best == INT32_MAX ? -1 : best;
+      chosen[j] = s_chosen[j];
+    }
+    __syncthreads();
   }
 }
 
@@ -326,10 +532,7 @@ static PrunePlan prune_plan(int32_t n, int32_t d, int32_t k, int32_t n_init) {
   return p;
 }
 
-static size_t kmeans_lds_bytes(int n, int d, int k) {
-  return (size_t)k * d * 8 + (size_t)n * 8 + KM_THREADS * 8 + (size_t)n * 4 + (size_t)k * 4 +
-         KM_THREADS * 4;
-}
+static size_t kmeans_lds_bytes(int n, int d, int k) { return (size_t)KmLayout(n, d, k).total; }
 
 static kt_status check_table(Ctx* h, int32_t n, int32_t d) {
   if (n < 1 || d < 1) return fail(h, KT_EINVAL, "empty time table");
