@@ -15,9 +15,9 @@
 //   G  = [1 0 0; 1/2 1/2 1/2; 1/2 -1/2 1/2; 0 0 1]
 //   At = [1 1 1 0; 0 1 -1 -1]
 //
-// Transform kernels are HBM-bound; each thread owns one channel (or output
-// channel) of one row / tile, so loads and stores run along the contiguous C
-// dimension.
+// Transform kernels are HBM-bound; each thread owns one or four channels (or
+// output channels) of one row / tile, so loads and stores run along the
+// contiguous C dimension.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -27,7 +27,7 @@ namespace kt {
 
 namespace {
 
-constexpr int CT = 256;            // threads per work-group of the transform kernels
+constexpr int CT = 128;            // threads per work-group of the transform kernels: small layers fill more CUs
 constexpr unsigned MAX_GRID = 65536;
 
 unsigned grid_for(int64_t work_groups) {
@@ -41,61 +41,93 @@ struct ConvDims {
   int32_t R, S, st, pad;
 };
 
-// One work-group per output row p (grid-stride); threads over the R*S*C columns.
+// The kernels below are written for an element type V and an index type I: four
+// neighbouring channels per thread (16-byte loads and stores) where the
+// channel count is a multiple of four and the buffers lie on 16-byte
+// boundaries, single floats otherwise; 32-bit indices while every buffer has
+// fewer than 2^31 elements.  All are HBM-bound on large layers; with one float
+// and three 64-bit divisions a thread they ran at the rate of the divisions.
+typedef float f32x4c __attribute__((ext_vector_type(4)));
+
+template <typename V>
+struct Lanes { static constexpr int N = 1; };
+template <>
+struct Lanes<f32x4c> { static constexpr int N = 4; };
+
+__device__ __forceinline__ float relu_of(float v) { return fmaxf(v, 0.f); }
+__device__ __forceinline__ f32x4c relu_of(f32x4c v) {
+  return f32x4c{fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f)};
+}
+__device__ __forceinline__ float max_of(float a, float b) { return fmaxf(a, b); }
+__device__ __forceinline__ f32x4c max_of(f32x4c a, f32x4c b) {
+  return f32x4c{fmaxf(a[0], b[0]), fmaxf(a[1], b[1]), fmaxf(a[2], b[2]), fmaxf(a[3], b[3])};
+}
+template <typename V>
+__device__ __forceinline__ V zero_of();
+template <>
+__device__ __forceinline__ float zero_of<float>() { return 0.f; }
+template <>
+__device__ __forceinline__ f32x4c zero_of<f32x4c>() { return f32x4c{0.f, 0.f, 0.f, 0.f}; }
+
+// Dimensions in elements of V along the channels.
+template <typename I>
+struct Dims {
+  I n, H, W, C, O, Ho, Wo, R, S, st, pad;
+};
+
+// Patch matrix: thread over (output position, filter position, channel).
+template <typename V, typename I>
 __global__ void __launch_bounds__(CT)
-im2col_kernel(const float* __restrict__ x, ConvDims d, float* __restrict__ col) {
-  const int64_t P = d.n * d.Ho * d.Wo;
-  const int64_t RSC = (int64_t)d.R * d.S * d.C;
-  for (int64_t p = blockIdx.x; p < P; p += gridDim.x) {
-    const int64_t b = p / (d.Ho * d.Wo);
-    const int64_t rem = p - b * d.Ho * d.Wo;
-    const int64_t i = rem / d.Wo, j = rem - (rem / d.Wo) * d.Wo;
-    float* out = col + p * RSC;
-    for (int64_t q = threadIdx.x; q < RSC; q += CT) {
-      const int64_t rs = q / d.C, c = q - rs * d.C;
-      const int64_t r = rs / d.S, s = rs - r * d.S;
-      const int64_t yi = i * d.st - d.pad + r, xj = j * d.st - d.pad + s;
-      float v = 0.f;
-      if (yi >= 0 && yi < d.H && xj >= 0 && xj < d.W) v = x[((b * d.H + yi) * d.W + xj) * d.C + c];
-      out[q] = v;
-    }
+im2col_kernel(const V* __restrict__ x, Dims<I> d, V* __restrict__ col) {
+  const I RSC = d.R * d.S * d.C;
+  const I total = d.n * d.Ho * d.Wo * RSC;
+  for (I e = (I)blockIdx.x * CT + threadIdx.x; e < total; e += (I)gridDim.x * CT) {
+    const I p = e / RSC, q = e - p * RSC;
+    const I rs = q / d.C, c = q - rs * d.C;
+    const I r = rs / d.S, s = rs - r * d.S;
+    const I bi = p / d.Wo, j = p - bi * d.Wo;
+    const I b = bi / d.Ho, i = bi - b * d.Ho;
+    const I yi = i * d.st - d.pad + r, xj = j * d.st - d.pad + s;
+    V v = zero_of<V>();
+    if (yi >= 0 && yi < d.H && xj >= 0 && xj < d.W) v = x[((b * d.H + yi) * d.W + xj) * d.C + c];
+    col[e] = v;
   }
 }
 
 // y[r][o] = act(y[r][o] + bias[o]) over rows x O.
+template <typename V, typename I>
 __global__ void __launch_bounds__(CT)
-bias_act_kernel(float* __restrict__ y, int64_t rows, int64_t O, const float* __restrict__ bias,
-                int32_t relu) {
-  const int64_t total = rows * O;
-  for (int64_t e = (int64_t)blockIdx.x * CT + threadIdx.x; e < total; e += (int64_t)gridDim.x * CT) {
-    float v = y[e];
+bias_act_kernel(V* __restrict__ y, I rows, I O, const V* __restrict__ bias, int32_t relu) {
+  const I total = rows * O;
+  for (I e = (I)blockIdx.x * CT + threadIdx.x; e < total; e += (I)gridDim.x * CT) {
+    V v = y[e];
     if (bias) v += bias[e % O];
-    y[e] = relu ? fmaxf(v, 0.f) : v;
+    y[e] = relu ? relu_of(v) : v;
   }
 }
 
 // V[k][t][c], k = 4u + v, for tile t = (b, ty, tx) and channel c.
+template <typename V, typename I>
 __global__ void __launch_bounds__(CT)
-wino_input_kernel(const float* __restrict__ x, ConvDims d, int64_t tH, int64_t tW,
-                  float* __restrict__ V) {
-  const int64_t T = d.n * tH * tW;
-  const int64_t total = T * d.C;
-  for (int64_t e = (int64_t)blockIdx.x * CT + threadIdx.x; e < total; e += (int64_t)gridDim.x * CT) {
-    const int64_t t = e / d.C, c = e - t * d.C;
-    const int64_t b = t / (tH * tW);
-    const int64_t rem = t - b * tH * tW;
-    const int64_t ty = rem / tW, tx = rem - ty * tW;
-    const int64_t y0 = 2 * ty - d.pad, x0 = 2 * tx - d.pad;
-    float v[4][4];
+wino_input_kernel(const V* __restrict__ x, Dims<I> d, I tH, I tW, V* __restrict__ out_all) {
+  const I T = d.n * tH * tW;
+  const I total = T * d.C;
+  for (I e = (I)blockIdx.x * CT + threadIdx.x; e < total; e += (I)gridDim.x * CT) {
+    const I t = e / d.C, c = e - t * d.C;
+    const I by = t / tW, tx = t - by * tW;
+    const I b = by / tH, ty = by - b * tH;
+    const I y0 = 2 * ty - d.pad, x0 = 2 * tx - d.pad;
+    V v[4][4];
 #pragma unroll
     for (int u = 0; u < 4; ++u)
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        const int64_t yi = y0 + u, xj = x0 + w;
-        v[u][w] = (yi >= 0 && yi < d.H && xj >= 0 && xj < d.W)
-                      ? x[((b * d.H + yi) * d.W + xj) * d.C + c] : 0.f;
+        const I yi = y0 + u, xj = x0 + w;
+        v[u][w] = zero_of<V>();
+        if (yi >= 0 && yi < d.H && xj >= 0 && xj < d.W)
+          v[u][w] = x[((b * d.H + yi) * d.W + xj) * d.C + c];
       }
-    float r[4][4];   // Bt d
+    V r[4][4];   // Bt d
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       r[0][w] = v[0][w] - v[2][w];
@@ -103,8 +135,8 @@ wino_input_kernel(const float* __restrict__ x, ConvDims d, int64_t tH, int64_t t
       r[2][w] = v[2][w] - v[1][w];
       r[3][w] = v[1][w] - v[3][w];
     }
-    const int64_t plane = T * d.C;
-    float* out = V + t * d.C + c;
+    const int64_t plane = (int64_t)total;
+    V* out = out_all + e;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {   // (Bt d) B
       out[(4 * u + 0) * plane] = r[u][0] - r[u][2];
@@ -145,55 +177,83 @@ wino_filter_kernel(const float* __restrict__ w, int64_t C, int64_t O, float* __r
 }
 
 // Y = At M A per tile and output channel, plus bias and activation.
+template <typename V, typename I>
 __global__ void __launch_bounds__(CT)
-wino_output_kernel(const float* __restrict__ Mm, ConvDims d, int64_t tH, int64_t tW,
-                   const float* __restrict__ bias, int32_t relu, float* __restrict__ y) {
-  const int64_t T = d.n * tH * tW;
-  const int64_t total = T * d.O;
-  const int64_t plane = total;
-  for (int64_t e = (int64_t)blockIdx.x * CT + threadIdx.x; e < total; e += (int64_t)gridDim.x * CT) {
-    const int64_t t = e / d.O, o = e - t * d.O;
-    float m[4][4];
+wino_output_kernel(const V* __restrict__ Mm, Dims<I> d, I tH, I tW, const V* __restrict__ bias,
+                   int32_t relu, V* __restrict__ y) {
+  const I T = d.n * tH * tW;
+  const I total = T * d.O;
+  const int64_t plane = (int64_t)total;
+  for (I e = (I)blockIdx.x * CT + threadIdx.x; e < total; e += (I)gridDim.x * CT) {
+    const I t = e / d.O, o = e - t * d.O;
+    V m[4][4];
 #pragma unroll
     for (int k = 0; k < 16; ++k) m[k / 4][k % 4] = Mm[k * plane + e];
-    float r[2][4];   // At M
+    V r[2][4];   // At M
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
       r[0][w] = m[0][w] + m[1][w] + m[2][w];
       r[1][w] = m[1][w] - m[2][w] - m[3][w];
     }
-    const int64_t b = t / (tH * tW);
-    const int64_t rem = t - b * tH * tW;
-    const int64_t ty = rem / tW, tx = rem - ty * tW;
-    const float bo = bias ? bias[o] : 0.f;
+    const I by = t / tW, tx = t - by * tW;
+    const I b = by / tH, ty = by - b * tH;
+    const V bo = bias ? bias[o] : zero_of<V>();
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
-      const float out2[2] = {r[u][0] + r[u][1] + r[u][2], r[u][1] - r[u][2] - r[u][3]};
+      const V out2[2] = {r[u][0] + r[u][1] + r[u][2], r[u][1] - r[u][2] - r[u][3]};
 #pragma unroll
       for (int w = 0; w < 2; ++w) {
-        const int64_t i = 2 * ty + u, j = 2 * tx + w;
+        const I i = 2 * ty + u, j = 2 * tx + w;
         if (i < d.Ho && j < d.Wo) {
-          const float v = out2[w] + bo;
-          y[((b * d.Ho + i) * d.Wo + j) * d.O + o] = relu ? fmaxf(v, 0.f) : v;
+          const V v = out2[w] + bo;
+          y[((b * d.Ho + i) * d.Wo + j) * d.O + o] = relu ? relu_of(v) : v;
         }
       }
     }
   }
 }
 
+template <typename V, typename I>
 __global__ void __launch_bounds__(CT)
-maxpool2x2_kernel(const float* __restrict__ x, int64_t n, int64_t H, int64_t W, int64_t C,
-                  float* __restrict__ y) {
-  const int64_t Ho = H / 2, Wo = W / 2;
-  const int64_t total = n * Ho * Wo * C;
-  for (int64_t e = (int64_t)blockIdx.x * CT + threadIdx.x; e < total; e += (int64_t)gridDim.x * CT) {
-    const int64_t c = e % C;
-    const int64_t q = e / C;
-    const int64_t j = q % Wo, i = (q / Wo) % Ho, b = q / (Wo * Ho);
-    const float* p = x + ((b * H + 2 * i) * W + 2 * j) * C + c;
-    const float v = fmaxf(fmaxf(p[0], p[C]), fmaxf(p[W * C], p[W * C + C]));
-    y[e] = v;
+maxpool2x2_kernel(const V* __restrict__ x, I n, I H, I W, I C, V* __restrict__ y) {
+  const I Ho = H / 2, Wo = W / 2;
+  const I total = n * Ho * Wo * C;
+  for (I e = (I)blockIdx.x * CT + threadIdx.x; e < total; e += (I)gridDim.x * CT) {
+    const I q = e / C, c = e - q * C;
+    const I bi = q / Wo, j = q - bi * Wo;
+    const I b = bi / Ho, i = bi - b * Ho;
+    const V* p = x + ((b * H + 2 * i) * W + 2 * j) * C + c;
+    y[e] = max_of(max_of(p[0], p[C]), max_of(p[W * C], p[W * C + C]));
   }
+}
+
+bool on16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
+
+template <typename I>
+Dims<I> dims_of(const ConvDims& d, int64_t lanes) {
+  return Dims<I>{(I)d.n, (I)d.H, (I)d.W, (I)(d.C / lanes), (I)(d.O / lanes), (I)d.Ho, (I)d.Wo,
+                 (I)d.R, (I)d.S, (I)d.st, (I)d.pad};
+}
+
+// Calls f with a value of the element type and one of the index type: four
+// channels a thread when `vec`, 32-bit indices when `small` (signed: the
+// coordinates go below zero in the padding).  With one float a thread and
+// 64-bit index divisions the address arithmetic bounds the transforms, not HBM: 8
+// images of 56x56x128 in, 128 out took 71 us in im2col, 16 and 12 us in the Winograd
+// input and output transforms; with four floats and 32-bit indices 34, 13 and 11.
+template <typename F>
+void with_types(bool vec, bool small, F f) {
+  if (vec && small) f(f32x4c{}, (int32_t)0);
+  else if (vec) f(f32x4c{}, (int64_t)0);
+  else if (small) f(0.f, (int32_t)0);
+  else f(0.f, (int64_t)0);
+}
+
+// Elements of every buffer a transform touches below 2^31 less the grid-stride
+// step, so no 32-bit index passes its range.
+bool fits32(int64_t a, int64_t b) {
+  constexpr int64_t LIMIT = (int64_t)0x7fffffff - (int64_t)MAX_GRID * CT;
+  return a < LIMIT && b < LIMIT;
 }
 
 kt_status check_conv(Ctx* h, kt_conv_algo algo, const kt_conv_shape* c, ConvDims* d) {
@@ -314,7 +374,14 @@ kt_status kt_conv2d(kt_handle hh, kt_conv_algo algo, const kt_conv_shape* c, con
   if (algo == KT_CONV_IM2COL) {
     const float* col = x;
     if (!pointwise(d)) {
-      hipLaunchKernelGGL(im2col_kernel, dim3(grid_for(gs.M)), dim3(CT), 0, s, x, d, (float*)ws);
+      with_types(d.C % 4 == 0 && on16(x) && on16(ws), fits32(gs.M * gs.K, d.n * d.H * d.W * d.C),
+                 [&](auto v, auto i) {
+        typedef decltype(v) V;
+        typedef decltype(i) I;
+        constexpr int N = Lanes<V>::N;
+        hipLaunchKernelGGL((im2col_kernel<V, I>), dim3(grid_for(cdiv(gs.M * gs.K / N, CT))), dim3(CT),
+                           0, s, (const V*)x, dims_of<I>(d, N), (V*)ws);
+      });
       if ((e = hipGetLastError()) != hipSuccess) return hip_fail(h, e, "im2col launch");
       col = (const float*)ws;
     }
@@ -347,8 +414,13 @@ kt_status kt_conv2d(kt_handle hh, kt_conv_algo algo, const kt_conv_shape* c, con
     }
     if (st != KT_OK) return st;
     if ((bias || relu) && !fused) {
-      hipLaunchKernelGGL(bias_act_kernel, dim3(grid_for(cdiv(gs.M * d.O, CT))), dim3(CT), 0, s, y,
-                         gs.M, d.O, bias, relu);
+      with_types(d.O % 4 == 0 && on16(y) && on16(bias), fits32(gs.M * d.O, 0), [&](auto v, auto i) {
+        typedef decltype(v) V;
+        typedef decltype(i) I;
+        constexpr int N = Lanes<V>::N;
+        hipLaunchKernelGGL((bias_act_kernel<V, I>), dim3(grid_for(cdiv(gs.M * d.O / N, CT))), dim3(CT),
+                           0, s, (V*)y, (I)gs.M, (I)(d.O / N), (const V*)bias, relu);
+      });
       if ((e = hipGetLastError()) != hipSuccess) return hip_fail(h, e, "bias launch");
     }
     return KT_OK;
@@ -364,8 +436,14 @@ kt_status kt_conv2d(kt_handle hh, kt_conv_algo algo, const kt_conv_shape* c, con
   char* after_v = ws + a256((size_t)16 * T * d.C * 4);
   const float* U = pre ? w : (const float*)after_v;
   float* Mm = (float*)(pre ? after_v : after_v + a256((size_t)16 * d.C * d.O * 4));
-  hipLaunchKernelGGL(wino_input_kernel, dim3(grid_for(cdiv(T * d.C, CT))), dim3(CT), 0, s, x, d,
-                     tH, tW, V);
+  with_types(d.C % 4 == 0 && on16(x) && on16(V), fits32(T * d.C, d.n * d.H * d.W * d.C),
+             [&](auto v, auto i) {
+    typedef decltype(v) E;
+    typedef decltype(i) I;
+    constexpr int N = Lanes<E>::N;
+    hipLaunchKernelGGL((wino_input_kernel<E, I>), dim3(grid_for(cdiv(T * d.C / N, CT))), dim3(CT), 0,
+                       s, (const E*)x, dims_of<I>(d, N), (I)tH, (I)tW, (E*)V);
+  });
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(h, e, "Winograd input launch");
   if (!pre) {
     hipLaunchKernelGGL(wino_filter_kernel, dim3(grid_for(cdiv(d.C * d.O, CT))), dim3(CT), 0, s, w,
@@ -376,8 +454,14 @@ kt_status kt_conv2d(kt_handle hh, kt_conv_algo algo, const kt_conv_shape* c, con
   st = launch_gemm(h, KT_F32, &gs, 1.f, V, d.C, T * d.C, U, d.O, d.C * d.O, 0.f, Mm, d.O, T * d.O,
                    nullptr, nullptr, cfg, s);
   if (st != KT_OK) return st;
-  hipLaunchKernelGGL(wino_output_kernel, dim3(grid_for(cdiv(T * d.O, CT))), dim3(CT), 0, s, Mm, d,
-                     tH, tW, bias, relu, y);
+  with_types(d.O % 4 == 0 && on16(Mm) && on16(y) && on16(bias), fits32(T * d.O, d.n * d.Ho * d.Wo * d.O),
+             [&](auto v, auto i) {
+    typedef decltype(v) E;
+    typedef decltype(i) I;
+    constexpr int N = Lanes<E>::N;
+    hipLaunchKernelGGL((wino_output_kernel<E, I>), dim3(grid_for(cdiv(T * d.O / N, CT))), dim3(CT), 0,
+                       s, (const E*)Mm, dims_of<I>(d, N), (I)tH, (I)tW, (const E*)bias, relu, (E*)y);
+  });
   if ((e = hipGetLastError()) != hipSuccess) return hip_fail(h, e, "Winograd output launch");
   return KT_OK;
 }
@@ -405,8 +489,13 @@ kt_status kt_maxpool2x2(kt_handle hh, const float* x, int64_t n, int64_t H, int6
   const int64_t total = n * (H / 2) * (W / 2) * C;
   if (total == 0) return KT_OK;
   if (!x || !y) return fail(h, KT_EINVAL, "x or y is NULL");
-  hipLaunchKernelGGL(maxpool2x2_kernel, dim3(grid_for(cdiv(total, CT))), dim3(CT), 0,
-                     (hipStream_t)stream, x, n, H, W, C, y);
+  with_types(C % 4 == 0 && on16(x) && on16(y), fits32(total, n * H * W * C), [&](auto v, auto i) {
+    typedef decltype(v) V;
+    typedef decltype(i) I;
+    constexpr int N = Lanes<V>::N;
+    hipLaunchKernelGGL((maxpool2x2_kernel<V, I>), dim3(grid_for(cdiv(total / N, CT))), dim3(CT), 0,
+                       (hipStream_t)stream, (const V*)x, (I)n, (I)H, (I)W, (I)(C / N), (V*)y);
+  });
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(h, e, "max-pool launch");
   return KT_OK;

@@ -13,34 +13,57 @@
 
 namespace kt {
 
-__global__ void cvt_bf16_kernel(const float* __restrict__ x, uint16_t* __restrict__ y, int64_t n) {
+// All three passes are HBM-bound and take 16 elements a thread and step, in
+// 16-byte loads and stores, when both buffers lie on 16-byte boundaries (the
+// elements after the last 16, and other buffers, one by one).
+// 4096 x 4096: BF16 17.2 -> 15.3 us, FP8 (both passes) 70.6 -> 34.4 us.
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4v __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t bf16_of(float x) {
+  const uint32_t u = __float_as_uint(x);
+  if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x007FFFFFu)) return (u >> 16) | 0x40u;
+  return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+}
+
+__global__ void __launch_bounds__(256)
+cvt_bf16_kernel(const float* __restrict__ x, uint16_t* __restrict__ y, int64_t n, int64_t nv) {
+  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const uint32_t u = __float_as_uint(x[i]);
-    uint16_t r;
-    if ((u & 0x7F800000u) == 0x7F800000u && (u & 0x007FFFFFu)) r = (uint16_t)((u >> 16) | 0x40u);
-    else r = (uint16_t)((u + 0x7FFFu + ((u >> 16) & 1u)) >> 16);
-    y[i] = r;
+  for (int64_t v = tid; v < nv; v += stride) {   // 8 elements: two loads, one store
+    const f32x4v a = reinterpret_cast<const f32x4v*>(x)[2 * v], b = reinterpret_cast<const f32x4v*>(x)[2 * v + 1];
+    u32x4v o;
+    o[0] = bf16_of(a[0]) | (bf16_of(a[1]) << 16);
+    o[1] = bf16_of(a[2]) | (bf16_of(a[3]) << 16);
+    o[2] = bf16_of(b[0]) | (bf16_of(b[1]) << 16);
+    o[3] = bf16_of(b[2]) | (bf16_of(b[3]) << 16);
+    reinterpret_cast<u32x4v*>(y)[v] = o;
   }
+  for (int64_t i = 8 * nv + tid; i < n; i += stride) y[i] = (uint16_t)bf16_of(x[i]);
 }
 
 __global__ void zero_u32_kernel(uint32_t* p) { *p = 0u; }
 
-__global__ void amax_kernel(const float* __restrict__ x, int64_t n, uint32_t* __restrict__ amax_bits) {
-  __shared__ uint32_t red[256];
+// |x| as bits: NaN sorts above infinity.
+__device__ __forceinline__ uint32_t abs_bits(float x) { return __float_as_uint(x) & 0x7FFFFFFFu; }
+
+__global__ void __launch_bounds__(256)
+amax_kernel(const float* __restrict__ x, int64_t n, int64_t nv, uint32_t* __restrict__ amax_bits) {
+  __shared__ uint32_t red[4];
   uint32_t m = 0u;
+  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const uint32_t u = __float_as_uint(x[i]) & 0x7FFFFFFFu;   // |x| (NaN sorts above inf)
-    m = u > m ? u : m;
+#pragma unroll 4
+  for (int64_t v = tid; v < nv; v += stride) {
+    const f32x4v a = reinterpret_cast<const f32x4v*>(x)[v];
+    m = max(m, max(max(abs_bits(a[0]), abs_bits(a[1])), max(abs_bits(a[2]), abs_bits(a[3]))));
   }
-  red[threadIdx.x] = m;
+  for (int64_t i = 4 * nv + tid; i < n; i += stride) m = max(m, abs_bits(x[i]));
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) m = max(m, (uint32_t)__shfl_xor((int)m, o));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
   __syncthreads();
-  for (int s = 128; s > 0; s >>= 1) {
-    if ((int)threadIdx.x < s && red[threadIdx.x + s] > red[threadIdx.x]) red[threadIdx.x] = red[threadIdx.x + s];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) atomicMax(amax_bits, red[0]);
+  if (threadIdx.x == 0) atomicMax(amax_bits, max(max(red[0], red[1]), max(red[2], red[3])));
 }
 
 __device__ __forceinline__ float fp8_scale_of(uint32_t amax_bits) {
@@ -48,29 +71,42 @@ __device__ __forceinline__ float fp8_scale_of(uint32_t amax_bits) {
   return amax > 0.f ? 448.0f / amax : 1.0f;
 }
 
-__global__ void quant_fp8_kernel(const float* __restrict__ x, int64_t n,
-                                 const uint32_t* __restrict__ amax_bits, uint8_t* __restrict__ y,
-                                 float* __restrict__ scale_out) {
-  const float s = fp8_scale_of(*amax_bits);
-  if (blockIdx.x == 0 && threadIdx.x == 0) *scale_out = s;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) {
-    const float v = x[i] * s;
-    uint8_t code;
-    if (v != v) {
-      code = 0x7F;
-    } else {
-      const float c = fminf(fmaxf(v, -448.0f), 448.0f);   // saturate, then round to nearest even
-      code = (uint8_t)(__builtin_amdgcn_cvt_pk_fp8_f32(c, 0.0f, 0, false) & 0xFF);
-    }
-    y[i] = code;
-  }
+// Two codes in the low 16 bits: saturate, then round to nearest even.
+__device__ __forceinline__ uint32_t fp8_pair(float a, float b) {
+  const float ca = fminf(fmaxf(a, -448.0f), 448.0f), cb = fminf(fmaxf(b, -448.0f), 448.0f);
+  uint32_t c = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(ca, cb, 0, false) & 0xFFFFu;
+  if (a != a) c = (c & 0xFF00u) | 0x7Fu;
+  if (b != b) c = (c & 0x00FFu) | 0x7F00u;
+  return c;
 }
 
-static unsigned grid_for(int64_t n) {
-  const int64_t b = (n + 255) / 256;
-  return (unsigned)(b < 4096 ? (b > 0 ? b : 1) : 4096);
+__global__ void __launch_bounds__(256)
+quant_fp8_kernel(const float* __restrict__ x, int64_t n, int64_t nv,
+                 const uint32_t* __restrict__ amax_bits, uint8_t* __restrict__ y,
+                 float* __restrict__ scale_out) {
+  const float s = fp8_scale_of(*amax_bits);
+  if (blockIdx.x == 0 && threadIdx.x == 0) *scale_out = s;
+  const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  for (int64_t v = tid; v < nv; v += stride) {   // 16 elements: four loads, one store
+    u32x4v o;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4v a = reinterpret_cast<const f32x4v*>(x)[4 * v + q];
+      o[q] = fp8_pair(a[0] * s, a[1] * s) | (fp8_pair(a[2] * s, a[3] * s) << 16);
+    }
+    reinterpret_cast<u32x4v*>(y)[v] = o;
+  }
+  for (int64_t i = 16 * nv + tid; i < n; i += stride) y[i] = (uint8_t)fp8_pair(x[i] * s, 0.0f);
 }
+
+// Work-groups for n threads' worth of steps, at most `most`.
+static unsigned grid_for(int64_t n, int64_t most) {
+  const int64_t b = (n + 255) / 256;
+  return (unsigned)(b < most ? (b > 0 ? b : 1) : most);
+}
+
+static bool on16(const void* p, const void* q) { return (((uintptr_t)p | (uintptr_t)q) & 15u) == 0; }
 
 }  // namespace kt
 
@@ -85,7 +121,9 @@ kt_status kt_convert_bf16(kt_handle hh, const float* x, int64_t n, uint16_t* y, 
   if (n < 0) return fail(h, KT_EINVAL, "n < 0");
   if (n == 0) return KT_OK;
   if (!x || !y) return fail(h, KT_EINVAL, "NULL buffer");
-  hipLaunchKernelGGL(cvt_bf16_kernel, dim3(grid_for(n)), dim3(256), 0, (hipStream_t)stream, x, y, n);
+  const int64_t nv = on16(x, y) ? n / 8 : 0;
+  hipLaunchKernelGGL(cvt_bf16_kernel, dim3(grid_for(nv > 0 ? nv : n, 4096)), dim3(256), 0,
+                     (hipStream_t)stream, x, y, n, nv);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(h, e, "BF16 conversion launch");
   return KT_OK;
@@ -103,9 +141,14 @@ kt_status kt_quantize_fp8(kt_handle hh, const float* x, int64_t n, uint8_t* y, f
   hipStream_t st = (hipStream_t)stream;
   uint32_t* amax = (uint32_t*)workspace;
   hipLaunchKernelGGL(zero_u32_kernel, dim3(1), dim3(1), 0, st, amax);
-  if (n > 0) hipLaunchKernelGGL(amax_kernel, dim3(grid_for(n)), dim3(256), 0, st, x, n, amax);
-  hipLaunchKernelGGL(quant_fp8_kernel, dim3(grid_for(n)), dim3(256), 0, st, x, n,
-                     (const uint32_t*)amax, y, d_scale);
+  // one atomic per work-group: four a CU are enough to keep the loads in flight
+  const int64_t na = on16(x, nullptr) ? n / 4 : 0;
+  if (n > 0)
+    hipLaunchKernelGGL(amax_kernel, dim3(grid_for(na > 0 ? na : n, 1024)), dim3(256), 0, st, x, n, na,
+                       amax);
+  const int64_t nv = on16(x, y) ? n / 16 : 0;
+  hipLaunchKernelGGL(quant_fp8_kernel, dim3(grid_for(nv > 0 ? nv : n, 4096)), dim3(256), 0, st, x, n,
+                     nv, (const uint32_t*)amax, y, d_scale);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return hip_fail(h, e, "FP8 quantization launch");
   return KT_OK;
