@@ -10,6 +10,7 @@
 // * Each operand keeps its stored layout in LDS: K-contiguous operands as
 //   [row][k] with 16-byte chunks XOR-swizzled by row (as the low-precision
 //   tiles), M/N-contiguous ones as [k][col].
+// * T = 8 with BK >= 16 multiplies on the BF16 matrix cores (SplitFrag below).
 // * The MFMA's K positions are assigned by lane group instead of
 //   interleaved: for the 32x32x2 MFMA lane half h takes k = h * BK / 2 + q at
 //   step q, for the 16x16x4 MFMA lane quarter g takes k = g * BK / 4 + q, so a
@@ -95,8 +96,86 @@ __device__ __forceinline__ float f32_at_mnmajor(const float* t, int k, int col) 
   return t[k * COLS + (((col >> 2) ^ f32_mswz<CPR, BK, T>(k)) << 2) + (col & 3)];
 }
 
+// FP32 products on the BF16 matrix cores (T = 8 with BK >= 16).  A float
+// is exactly the sum of three BF16 values, x = h + m + l (each the rounding of
+// what is left: 24 bits as 8 + 8 + 8), and
+//   a b = ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + terms < 2^-25 |a b|,
+// so six BF16 MFMAs, whose products are exact and whose sums are FP32, take
+// the place of the eight times slower FP32 ones.  Each 16-deep step adds the
+// small products first.  The result is nearer to the exact product than the
+// FP32 MFMA's, which rounds after every k: relative error against FP64 of
+// normal operands at K = 16 / 128 / 1024 / 4096: 3.4e-8 / 1.65e-7 / 4.9e-7 /
+// 1.00e-6, with FP32 MFMAs 7.3e-8 / 2.04e-7 / 5.7e-7 / 1.15e-6.  (Truncated
+// instead of rounded pieces bias the sums: 9.5e-6 for positive operands at
+// K = 4096.)  Below K = 5 the six sums round more often than the few FP32
+// ones: products with K < 16 keep the FP32 MFMAs (launch_gemm_f32).
+//
+// A lane splits (64 + 64) * 16 / 64 values for 24 MFMAs a step: about 200
+// vector instructions (800 clocks) beside 768 clocks of MFMA, so the split of
+// step g + 1 is placed between the MFMAs of step g; one after the other the
+// two took turns (MFMA busy 50 %, now 57 %; the clock falls to 1.7 GHz under
+// this load, which bounds it).  Subtraction with a shift, not v_dot2_f32_bf16,
+// makes the residuals: the dot unit shares the matrix pipe.  32x32 wave blocks
+// (T = 4) split twice as many values per MFMA and gained nothing.
+// 128x128 tiles, BK = 32: 4096^3 NT 1051 -> 750 us (131 -> 183 TFLOP/s), NN
+// 1160 -> 803 us; 2048x1024x1536 batch 16 TN 813 -> 610 us.
+//
+// Two kinds of operand do not split: infinities, NaN and values that round
+// to infinity in BF16, whose residual is NaN, and rows or columns whose
+// largest element is so small that the pieces fall below BF16's range.  A
+// wave that meets either (a non-finite sum; a nonzero row with every exponent
+// below 2^-95) computes its block again with FP32 MFMAs straight from memory.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+struct SplitFrag {
+  bf16x8 h, m, l;
+
+  __device__ __forceinline__ void pin() { asm volatile("" : "+v"(h), "+v"(m), "+v"(l)); }
+  __device__ __forceinline__ static float low(bf16x2 v) {
+    return __uint_as_float(__builtin_bit_cast(uint32_t, v) << 16);
+  }
+  __device__ __forceinline__ static float high(bf16x2 v) {
+    return __uint_as_float(__builtin_bit_cast(uint32_t, v) & 0xffff0000u);
+  }
+
+  // Values 2 p and 2 p + 1; bits collects the OR of their bit patterns (its
+  // exponent field is at least the largest exponent, and below a power of two
+  // exactly when all are).
+  __device__ __forceinline__ void set(int p, const float a, const float b, uint32_t& bits) {
+    bits |= __float_as_uint(a) | __float_as_uint(b);
+    const bf16x2 hp = __builtin_convertvector(f32x2{a, b}, bf16x2);
+    const float ra = a - low(hp), rb = b - high(hp);   // exact
+    const bf16x2 mp = __builtin_convertvector(f32x2{ra, rb}, bf16x2);
+    const float qa = ra - low(mp), qb = rb - high(mp);
+    const bf16x2 lp = __builtin_convertvector(f32x2{qa, qb}, bf16x2);
+    h[2 * p] = hp[0]; h[2 * p + 1] = hp[1];
+    m[2 * p] = mp[0]; m[2 * p + 1] = mp[1];
+    l[2 * p] = lp[0]; l[2 * p + 1] = lp[1];
+  }
+};
+
+__device__ __forceinline__ bool splits_too_small(uint32_t bits) {
+  return (bits & 0x7fffffffu) != 0u && (bits & 0x7f800000u) < (32u << 23);
+}
+
+
+template <int T, int BK>
+struct F32Split {
+  static constexpr bool value = T == 8 && BK >= 16;
+};
+
+// At least two waves per SIMD for the split kernels: with that register
+// budget the accumulators stay out of the AGPRs (and of copies to and from
+// them).
+template <int T, int BK>
+struct F32DmaOcc {
+  static constexpr int value = F32Split<T, BK>::value ? 2 : 1;
+};
+
 template <int BM, int BN, int T, int BK, int TA, int TB>
 __global__ void __launch_bounds__(BM * BN / (T * T))
+__attribute__((amdgpu_waves_per_eu(F32DmaOcc<T, BK>::value, 8)))
 gemm_f32_dma_kernel(GemmArgs args) {
   using Cfg = F32DmaCfg<BM, BN, T, BK, TA, TB>;
   constexpr int NS = Cfg::NS;
@@ -144,9 +223,24 @@ gemm_f32_dma_kernel(GemmArgs args) {
   };
 
   constexpr int NACC = (T == 2) ? 4 : (T == 4) ? 16 : 64;
-  float acc[NACC];
+  constexpr bool SPLIT = F32Split<T, BK>::value;
+  constexpr int SUB = 2;   // 32x32 blocks per wave edge (split kernels)
+  float acc[SPLIT ? 1 : NACC];
+  f32x16 sacc[SUB][SUB];
+  uint32_t bits_a[SUB], bits_b[SUB];
+  if constexpr (SPLIT) {
 #pragma unroll
-  for (int i = 0; i < NACC; ++i) acc[i] = 0.f;
+    for (int i = 0; i < SUB; ++i) {
+      bits_a[i] = bits_b[i] = 0u;
+#pragma unroll
+      for (int j = 0; j < SUB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sacc[i][j][r] = 0.f;
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < NACC; ++i) acc[i] = 0.f;
+  }
 
   const int nk = (int)((K + BK - 1) / BK);
   const int my_blocks = (wave < Cfg::NBLK % Cfg::WAVES || Cfg::NBLK % Cfg::WAVES == 0)
@@ -155,8 +249,11 @@ gemm_f32_dma_kernel(GemmArgs args) {
   for (int s = 0; s < NS - 1; ++s)
     if (s < nk) src.issue(args, m0, n0, lds0 + s * Cfg::STAGE);
 
-  for (int kt = 0; kt < nk; ++kt) {
-    const int ahead = min(NS - 2, nk - 1 - kt);
+  // Make stage kt readable: its DMA has landed for every wave, K beyond the
+  // product is zero, and the stage AHEAD stages on is on its way into the
+  // buffer that every wave has finished reading.
+  auto open_stage = [&](int kt, int issued, int ahead_max) {
+    const int ahead = min(ahead_max, nk - 1 - kt);
     if (my_blocks == Cfg::NW_HI) wait_stage<Cfg::NW_HI, NS>(ahead);
     else wait_stage<Cfg::NW_LO, NS>(ahead);
     char* cur = lds + (kt % NS) * Cfg::STAGE;
@@ -164,8 +261,89 @@ gemm_f32_dma_kernel(GemmArgs args) {
       f32_dma_zero_tail<BM, BN, T, BK, TA, TB>(cur, (int)(K - (int64_t)kt * BK), tid);
       vm_wait_barrier<0>();
     }
-    if (kt + NS - 1 < nk)
-      src.issue(args, m0, n0, lds0 + ((kt + NS - 1) % NS) * Cfg::STAGE);
+    if (issued < nk) src.issue(args, m0, n0, lds0 + (issued % NS) * Cfg::STAGE);
+  };
+  if constexpr (SPLIT) {
+    // 32x32x16 MFMAs: lane half h takes k = h * BK / 2 + 8 s .. + 7 at step s.
+    // The fragments of step g + 1 are read and split while the MFMAs of step
+    // g run.
+    constexpr int S = BK / 16;   // steps per stage
+    const int r32 = lane & 31, h = lane >> 5;
+    const int steps = nk * S;
+    struct Frags { SplitFrag a[SUB], b[SUB]; };
+    Frags f0, f1;
+    f32x4 xa[SUB][2], xb[SUB][2];
+    auto fetch = [&](int g) {
+      const char* cur = lds + ((g / S) % NS) * Cfg::STAGE;
+      const float* as = reinterpret_cast<const float*>(cur);
+      const float* bs = reinterpret_cast<const float*>(cur + Cfg::A_BYTES);
+      const int k = h * (BK / 2) + 8 * (g % S);
+#pragma unroll
+      for (int i = 0; i < SUB; ++i)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+          xa[i][q] = A4(as, wm0 + 32 * i + r32, k + 4 * q);
+          xb[i][q] = B4(bs, wn0 + 32 * i + r32, k + 4 * q);
+        }
+    };
+    // pair u (0 .. 8 SUB - 1) of the fetched values: 4 of each fragment
+    auto split = [&](Frags& f, int u) {
+      const int i = u / 8, p = u % 4;
+      if (u % 8 < 4) f.a[i].set(p, xa[i][p / 2][2 * (p % 2)], xa[i][p / 2][2 * (p % 2) + 1], bits_a[i]);
+      else f.b[i].set(p, xb[i][p / 2][2 * (p % 2)], xb[i][p / 2][2 * (p % 2) + 1], bits_b[i]);
+    };
+    // MFMA u of a step: six products, the small ones first, of every block
+    auto mfma = [&](const Frags& f, int u) {
+      const int i = u / SUB % SUB, j = u % SUB, w = u / (SUB * SUB);
+      const bf16x8 a = w == 0 ? f.a[i].l : (w == 2 || w == 3) ? f.a[i].m : f.a[i].h;
+      const bf16x8 b = w == 1 ? f.b[j].l : (w == 2 || w == 4) ? f.b[j].m : f.b[j].h;
+      sacc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, sacc[i][j], 0, 0, 0);
+    };
+    constexpr int NM = 6 * SUB * SUB, NP = 8 * SUB;
+    constexpr int LEAD = NM - NP > 0 ? NM - NP : 0;   // MFMAs over the latency of the reads
+    auto step = [&](const Frags& cur, Frags& next, int g) {
+      if (g % S == 0) open_stage(g / S, g / S + NS - 1, NS - 2);
+      fetch(g);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < LEAD; ++u) mfma(cur, u);
+#pragma unroll
+      for (int u = 0; u < (NM - LEAD > NP ? NM - LEAD : NP); ++u) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (LEAD + u < NM) mfma(cur, LEAD + u);
+        if (u < NP) split(next, u);
+      }
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) {   // done here, not sunk to their use in the next step
+        next.a[i].pin();
+        next.b[i].pin();
+      }
+    };
+    auto last = [&](const Frags& cur) {
+#pragma unroll
+      for (int u = 0; u < NM; ++u) mfma(cur, u);
+    };
+    if (nk > 0) {
+      open_stage(0, NS - 1, NS - 2);
+      fetch(0);
+#pragma unroll
+      for (int u = 0; u < NP; ++u) split(f0, u);
+      int g = 0;
+      for (; g + 2 < steps; g += 2) {
+        step(f0, f1, g + 1);
+        step(f1, f0, g + 2);
+      }
+      if (g + 1 < steps) {
+        step(f0, f1, g + 1);
+        last(f1);
+      } else {
+        last(f0);
+      }
+    }
+  }
+  for (int kt = 0; kt < (SPLIT ? 0 : nk); ++kt) {
+    open_stage(kt, kt + NS - 1, NS - 2);
+    char* cur = lds + (kt % NS) * Cfg::STAGE;
     const float* as = reinterpret_cast<const float*>(cur);
     const float* bs = reinterpret_cast<const float*>(cur + Cfg::A_BYTES);
     if constexpr (T == 2) {
@@ -240,7 +418,75 @@ gemm_f32_dma_kernel(GemmArgs args) {
       *p = out;
     }
   };
-  if constexpr (T == 2) {
+  auto put_blocks = [&](const f32x16 (&c)[SUB][SUB]) {
+#pragma unroll
+    for (int i = 0; i < SUB; ++i)
+#pragma unroll
+      for (int j = 0; j < SUB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          put(32 * i + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), 32 * j + (lane & 31), c[i][j][r]);
+  };
+  if constexpr (SPLIT) {
+    const int r32 = lane & 31, h = lane >> 5;
+    float nan = 0.f;   // becomes NaN when a sum is not finite
+    bool redo = false;
+    // only rows and columns of the product count: beyond them lies whatever
+    // the operands' memory holds
+    const int rows = (int)min(M - m0 - wm0, (int64_t)(32 * SUB)), cols = (int)min(N - n0 - wn0, (int64_t)(32 * SUB));
+#pragma unroll
+    for (int i = 0; i < SUB; ++i) {
+      // both lane halves hold K positions of row / column r32
+      const uint32_t ba = bits_a[i] | (uint32_t)__shfl_xor((int)bits_a[i], 32);
+      const uint32_t bb = bits_b[i] | (uint32_t)__shfl_xor((int)bits_b[i], 32);
+      redo = redo || (32 * i + r32 < rows && splits_too_small(ba)) ||
+             (32 * i + r32 < cols && splits_too_small(bb));
+#pragma unroll
+      for (int j = 0; j < SUB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const bool stored = 32 * i + (r >> 2) * 8 + h * 4 + (r & 3) < rows && 32 * j + r32 < cols;
+          nan = fmaf(stored ? sacc[i][j][r] : 0.f, 0.f, nan);
+        }
+    }
+    if (__any(redo || nan != nan)) {   // wave-uniform
+      const float* Af = static_cast<const float*>(args.A) + bz * args.sA;
+      const float* Bf = static_cast<const float*>(args.B) + bz * args.sB;
+      const float *pa[SUB], *pb[SUB];
+      f32x16 c[SUB][SUB];
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) {
+        pa[i] = Af + min(m0 + wm0 + 32 * i + r32, M - 1) * (TA == 0 ? args.lda : 1);
+        pb[i] = Bf + min(n0 + wn0 + 32 * i + r32, N - 1) * (TB == 1 ? args.ldb : 1);
+#pragma unroll
+        for (int j = 0; j < SUB; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) c[i][j][r] = 0.f;
+      }
+      const int64_t ka = TA == 0 ? 1 : args.lda, kb = TB == 1 ? 1 : args.ldb;
+#pragma nounroll
+      for (int64_t k0 = 0; k0 < K; k0 += 2) {
+        const int64_t k = k0 + h;
+        float a[SUB], b[SUB];
+#pragma unroll
+        for (int i = 0; i < SUB; ++i) {
+          a[i] = k < K ? pa[i][k * ka] : 0.f;
+          b[i] = k < K ? pb[i][k * kb] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < SUB; ++i)
+#pragma unroll
+          for (int j = 0; j < SUB; ++j)
+            c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], c[i][j], 0, 0, 0);
+      }
+      put_blocks(c);
+      return;
+    }
+  }
+
+  if constexpr (SPLIT) {
+    put_blocks(sacc);
+  } else if constexpr (T == 2) {
 #pragma unroll
     for (int r = 0; r < 4; ++r) put((lane >> 4) * 4 + r, lane & 15, acc[r]);
   } else if constexpr (T == 4) {
@@ -267,12 +513,13 @@ struct F32DmaServes {
 
 // Host-side launcher of one instantiation on a stream: operands whose rows
 // all start on 16-byte boundaries take the DMA pipeline where the
-// configuration has one, any other the register-staged kernel.
+// configuration has one (the split kernels from K = 16: less deep products
+// are more exact with FP32 MFMAs), any other the register-staged kernel.
 template <int BM, int BN, int T, int BK, int TA, int TB>
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t stream) {
   using Cfg = GemmF32Cfg<BM, BN, T, BK, TA, TB>;
   if constexpr (F32DmaServes<BM, BN, T, BK>::value) {
-    if (a.vecA == LP_ALIGN_DMA && a.vecB == LP_ALIGN_DMA)
+    if (a.vecA == LP_ALIGN_DMA && a.vecB == LP_ALIGN_DMA && (!F32Split<T, BK>::value || a.K >= 16))
       return launch_flat<4>(gemm_f32_dma_kernel<BM, BN, T, BK, TA, TB>, a, BM, BN, Cfg::NT, stream);
   }
   return launch_flat<4>(gemm_f32_kernel<BM, BN, T, BK, TA, TB>, a, BM, BN, Cfg::NT, stream);
