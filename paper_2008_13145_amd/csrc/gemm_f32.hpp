@@ -48,7 +48,8 @@ struct GemmArgs {
   float* C; int64_t ldc, sC;
   float alpha, beta;
   const float* scaleA; const float* scaleB;   // FP8 only
-  int32_t vecA, vecB;   // low-precision paths: row alignment mode (LP_ALIGN_*)
+  int32_t vecA, vecB;   // row alignment mode of each operand (LP_ALIGN_*)
+  int32_t ragged;       // FP32 DMA kernels: some operand row is not on a 16-byte boundary
   int32_t tiles_m, tiles_n;
   uint32_t blocks;      // tiles_m * tiles_n * batch of this launch
   FastDiv per_item;     // by tiles_m * tiles_n

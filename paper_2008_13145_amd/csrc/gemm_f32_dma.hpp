@@ -1,6 +1,6 @@
 // LDS-DMA pipeline of the FP32 family (T = 2, 4, 8), taken when every
-// operand row starts on a 16-byte boundary and no 16-byte read leaves an
-// operand (the same rule as the low-precision family, with 4-float chunks).
+// operand row starts on a 4-byte boundary and holds a 16-byte chunk
+// (launch_gemm_f32); no 16-byte read leaves an operand.
 // Same configuration knobs and results contract as gemm_f32.hpp; the
 // differences:
 //
@@ -257,6 +257,8 @@ gemm_f32_dma_kernel(GemmArgs args) {
     if (my_blocks == Cfg::NW_HI) wait_stage<Cfg::NW_HI, NS>(ahead);
     else wait_stage<Cfg::NW_LO, NS>(ahead);
     char* cur = lds + (kt % NS) * Cfg::STAGE;
+    if (kt == nk - 1 && src.settle(args, m0, n0, (int)(K - (int64_t)kt * BK), cur, tid))
+      vm_wait_barrier<0>();
     if (kt == nk - 1 && K - (int64_t)kt * BK < BK) {
       f32_dma_zero_tail<BM, BN, T, BK, TA, TB>(cur, (int)(K - (int64_t)kt * BK), tid);
       vm_wait_barrier<0>();
@@ -511,16 +513,25 @@ struct F32DmaServes {
   static constexpr bool value = T >= 2 && (BM * BK * 4) % 1024 == 0 && (BN * BK * 4) % 1024 == 0;
 };
 
-// Host-side launcher of one instantiation on a stream: operands whose rows
-// all start on 16-byte boundaries take the DMA pipeline where the
-// configuration has one (the split kernels from K = 16: less deep products
-// are more exact with FP32 MFMAs), any other the register-staged kernel.
+// Host-side launcher of one instantiation on a stream.  Operands whose rows
+// start on 4-byte boundaries and hold at least one 16-byte chunk take the DMA
+// pipeline where the configuration has one (the split kernels from K = 16:
+// less deep products are more exact with FP32 MFMAs): global loads need
+// dword alignment only, a chunk that runs over the end of its row reads into
+// the next one, and only the chunk at the very end of an operand is moved
+// (DmaSource::settle).  Any other operand takes the register-staged kernel.
+// Dense 1001x1003x1005 NN: (32, 32, 2, 32) 37.5 -> 28.1 us, (64, 64, 4, 32)
+// 45.9 -> 33.0 us, (128, 128, 8, 16) 134 -> 57 us (the last on the split kernel).
 template <int BM, int BN, int T, int BK, int TA, int TB>
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t stream) {
   using Cfg = GemmF32Cfg<BM, BN, T, BK, TA, TB>;
   if constexpr (F32DmaServes<BM, BN, T, BK>::value) {
-    if (a.vecA == LP_ALIGN_DMA && a.vecB == LP_ALIGN_DMA && (!F32Split<T, BK>::value || a.K >= 16))
-      return launch_flat<4>(gemm_f32_dma_kernel<BM, BN, T, BK, TA, TB>, a, BM, BN, Cfg::NT, stream);
+    if (a.vecA >= LP_ALIGN_ROWS && a.vecB >= LP_ALIGN_ROWS && a.K >= (F32Split<T, BK>::value ? 16 : 4) &&
+        (TA == 0 || a.M >= 4) && (TB == 1 || a.N >= 4)) {
+      GemmArgs g = a;
+      g.ragged = a.vecA != LP_ALIGN_DMA || a.vecB != LP_ALIGN_DMA;
+      return launch_flat<4>(gemm_f32_dma_kernel<BM, BN, T, BK, TA, TB>, g, BM, BN, Cfg::NT, stream);
+    }
   }
   return launch_flat<4>(gemm_f32_kernel<BM, BN, T, BK, TA, TB>, a, BM, BN, Cfg::NT, stream);
 }

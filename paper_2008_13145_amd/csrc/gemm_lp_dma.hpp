@@ -167,6 +167,7 @@ struct DmaSource {
   int whole;                           // whole stages left to issue
   int tail;                            // K positions of the stage after them
   bool offsets;                        // the 32-bit offsets hold
+  bool ragged;                         // rows on 4-byte boundaries only (GemmArgs::ragged)
 
   // Chunk of block q this lane moves: tile row (K-major) or k (M/N-major)
   // and element column.
@@ -222,6 +223,7 @@ struct DmaSource {
     constexpr int LOG_A = 31 - __builtin_ctz((TA == 0 ? BM : BK) * EB);
     constexpr int LOG_B = 31 - __builtin_ctz((TB == 1 ? BN : BK) * EB);
     offsets = (((uint64_t)g.lda >> LOG_A) | ((uint64_t)g.ldb >> LOG_B)) == 0;
+    ragged = EB == 4 && g.ragged != 0;
     const uint64_t over_m = (uint64_t)(g.M - m0), over_n = (uint64_t)(g.N - n0);
     const int left_m = (over_m >> 31) ? BM : min(BM, (int)over_m);
     const int left_n = (over_n >> 31) ? BN : min(BN, (int)over_n);
@@ -240,7 +242,8 @@ struct DmaSource {
 
   // Issue the next stage into the LDS at byte address `stage`.
   __device__ __forceinline__ void issue(const GemmArgs& g, int64_t m0, int64_t n0, uint32_t stage) {
-    if (offsets) {
+    const bool last = whole <= (tail == 0 ? 1 : 0);
+    if (offsets && !(ragged && last)) {
       if (whole > 0) {
 #pragma unroll
         for (int i = 0; i < Cfg::NW_HI; ++i)
@@ -253,7 +256,8 @@ struct DmaSource {
             lds_dma16(of_a(i) ? a : b, in_tail(g, i), stage + (wave + i * Cfg::WAVES) * 1024);
       }
     } else {
-      // whole addresses: a loop, out of the way of the products that have offsets
+      // whole addresses: a loop, out of the way of the products that have
+      // offsets; the last stage of a ragged product
       const int left_k = whole > 0 ? BK : tail;
 #pragma nounroll
       for (int q = wave; q < Cfg::NBLK; q += Cfg::WAVES) {
@@ -266,9 +270,11 @@ struct DmaSource {
         if (kmajor) {
           row = min(row, left - 1);
           c = min(col, (left_k - 1) / CE * CE);       // chunks beyond K: the last one
+          if (ragged && last && row == left - 1) c = min(c, (int64_t)left_k - CE);
         } else {
           row = min(r, left_k - 1);
           c = min(c, (left - 1) / CE * CE);           // chunks beyond the extent: the last one
+          if (ragged && last && row == left_k - 1) c = min(c, left - CE);
         }
         lds_dma16((is_a ? a : b) + (row * ld + c) * EB, stage + q * 1024);
       }
@@ -276,6 +282,30 @@ struct DmaSource {
     a += step_a;
     b += step_b;
     --whole;
+  }
+
+  // The chunk at the very end of a ragged operand was read so that it ends
+  // with the operand (every other chunk that runs over its row's extent stays
+  // inside the next row); move its values to their places.  Called for the
+  // last stage, landed, by every thread; true when a barrier is needed after.
+  __device__ __forceinline__ bool settle(const GemmArgs& g, int64_t m0, int64_t n0, int left_k,
+                                         char* stage, int tid) const {
+    if (!ragged) return false;
+    if (tid < 2) {   // one thread per operand
+      const bool is_a = tid == 0, kmajor = is_a ? (TA == 0) : (TB == 1);
+      const int64_t left = is_a ? g.M - m0 : g.N - n0;
+      const int rows = is_a ? BM : BN;
+      if (left <= rows) {   // the tile that holds the operand's last row or column
+        const int ext = kmajor ? left_k : (int)left;
+        const int c = (ext - 1) / CE * CE, shift = c + CE - ext;
+        const int r = kmajor ? (int)left - 1 : left_k - 1;
+        const int sw = kmajor ? Swz::k(r) : is_a ? Swz::mn_a(r) : Swz::mn_b(r);
+        float* p = reinterpret_cast<float*>(stage + (is_a ? 0 : Cfg::A_BYTES)) +
+                   r * (kmajor ? BK : rows) + ((c / CE) ^ sw) * CE;
+        for (int e = 0; e + shift < CE; ++e) p[e] = p[e + shift];
+      }
+    }
+    return true;
   }
 };
 

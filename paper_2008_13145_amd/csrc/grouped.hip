@@ -116,7 +116,7 @@ grouped_bf16_kernel(const GroupDesc* __restrict__ descs, const WorkItem* __restr
     a.C = d.C; a.ldc = d.ldc; a.sC = 0;
     a.alpha = alpha; a.beta = beta;
     a.scaleA = nullptr; a.scaleB = nullptr;
-    a.vecA = d.vecA; a.vecB = d.vecB;
+    a.vecA = d.vecA; a.vecB = d.vecB; a.ragged = 0;
     a.tiles_m = 0; a.tiles_n = 0;
     if constexpr (TWO) {
       if (it.cls == 0) Big::run(a, it.tm, it.tn, d.dma != 0, lds);
