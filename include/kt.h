@@ -166,7 +166,9 @@ kt_status kt_set_workspace(kt_handle h, void* workspace, size_t bytes);
  * config_id >= 0 forces that kernel (a configuration or a split-K variant,
  * see kt_num_kernels; a variant takes its partial planes from the workspace
  * set with kt_set_workspace); -1 asks the fitted selector, whose pick may be
- * a split-K variant.
+ * a split-K variant.  With -1, an FP32 product of batch 1 with K >= 1536 and at
+ * most 128 tiles of the picked configuration runs in 4 or 8 slices of K when
+ * that workspace holds their partial planes.
  * With beta == 0, C is never read (NaN in C does not propagate).  M, N or
  * batch == 0 is a no-op; K == 0 gives C = beta * C.  Unaligned pointers or
  * leading dimensions are never an error (FP32 rows load as dword-aligned

@@ -295,6 +295,14 @@ kt_status kt_gemm(kt_handle hh, kt_dtype in_dtype, const kt_shape* s, float alph
     if (st != KT_OK) return st;
   }
   if (!valid_kernel(h, in_dtype, id)) return fail(h, KT_EINVAL, "kernel id out of range");
+  if (config_id < 0) {
+    const int32_t slices = deep_slices(h, in_dtype, s, id);
+    const size_t planes = split_plane_bytes(s, slices);
+    if (planes > 0 && h->gemm_ws && h->gemm_ws_bytes >= planes)
+      return splitk_gemm(h, in_dtype, s, slices, alpha, A, lda, strideA, B, ldb, strideB, beta, C, ldc,
+                         strideC, scaleA, scaleB, id, h->gemm_ws, h->gemm_ws_bytes, stream, nullptr,
+                         nullptr, 0, nullptr);
+  }
   return run_kernel(h, in_dtype, s, alpha, A, lda, strideA, B, ldb, strideB, beta, C, ldc,
                     strideC, scaleA, scaleB, id, h->gemm_ws, h->gemm_ws_bytes, (hipStream_t)stream);
 }

@@ -226,6 +226,7 @@ gemm_f32_dma_kernel(GemmArgs args) {
   constexpr bool SPLIT = F32Split<T, BK>::value;
   constexpr int SUB = 2;   // 32x32 blocks per wave edge (split kernels)
   float acc[SPLIT ? 1 : NACC];
+  float total[T == 2 ? 4 : 1] = {};
   f32x16 sacc[SUB][SUB];
   uint32_t bits_a[SUB], bits_b[SUB];
   if constexpr (SPLIT) {
@@ -343,67 +344,87 @@ gemm_f32_dma_kernel(GemmArgs args) {
       }
     }
   }
-  for (int kt = 0; kt < (SPLIT ? 0 : nk); ++kt) {
-    open_stage(kt, kt + NS - 1, NS - 2);
-    char* cur = lds + (kt % NS) * Cfg::STAGE;
-    const float* as = reinterpret_cast<const float*>(cur);
-    const float* bs = reinterpret_cast<const float*>(cur + Cfg::A_BYTES);
-    if constexpr (T == 2) {
-      // 16x16x4: lane quarter g = lane / 16 takes k = g * BK / 4 + q
-      const int r16 = lane & 15, g = lane >> 4;
-      constexpr int KQ = BK / 4;
-      f32x4 c = {acc[0], acc[1], acc[2], acc[3]};
-      // element reads, which the compiler merges where it can (explicit
-      // 16-byte reads measured 3 % slower here on the mixed layouts)
+  // T = 2 carries its running sums to `total` every 256 of K: a chain of K / 4
+  // rounded additions is what deep products lose most by (1021 x 515 x 997:
+  // 5.6e-7 against 64 bits in one chain, 2.9e-7 in blocks).
+  constexpr int SUM_STAGES = T == 2 ? 256 / BK : INT_MAX;
+  for (int kt = 0; kt < (SPLIT ? 0 : nk);) {
+    const int end = T == 2 ? min(nk, kt + SUM_STAGES) : nk;
+    for (; kt < end; ++kt) {
+      open_stage(kt, kt + NS - 1, NS - 2);
+      char* cur = lds + (kt % NS) * Cfg::STAGE;
+      const float* as = reinterpret_cast<const float*>(cur);
+      const float* bs = reinterpret_cast<const float*>(cur + Cfg::A_BYTES);
+      if constexpr (T == 2) {
+        // 16x16x4: lane quarter g = lane / 16 takes k = g * BK / 4 + q
+        const int r16 = lane & 15, g = lane >> 4;
+        constexpr int KQ = BK / 4;
+        f32x4 c = {acc[0], acc[1], acc[2], acc[3]};
+        // element reads, which the compiler merges where it can (explicit
+        // 16-byte reads measured 3 % slower here on the mixed layouts); 64 deep,
+        // all in flight before the first MFMA (left to the scheduler, each
+        // MFMA group waited for its own: 1021x515x997 NT 54.6 -> 50.6 us, 4 x
+        // 1x4096x6272 81 -> 75 us on (32, 32, 2, 64); 32 deep it gains nothing)
+        float a[KQ], b[KQ];
 #pragma unroll
-      for (int q = 0; q < KQ; ++q) {
-        const float a = A_at(as, wm0 + r16, g * KQ + q);
-        const float b = B_at(bs, wn0 + r16, g * KQ + q);
-        c = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-      }
+        for (int q = 0; q < KQ; ++q) {
+          a[q] = A_at(as, wm0 + r16, g * KQ + q);
+          b[q] = B_at(bs, wn0 + r16, g * KQ + q);
+        }
+        if (BK >= 64) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc[r] = c[r];
-    } else if constexpr (T == 4) {
-      const int r32 = lane & 31, h = lane >> 5;
-      constexpr int KH = BK / 2;
-      f32x16 c;
+        for (int q = 0; q < KQ; ++q) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[q], c, 0, 0, 0);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) c[r] = acc[r];
-      static_assert(KH % 4 == 0, "whole 16-byte chunks per lane half");
+        for (int r = 0; r < 4; ++r) acc[r] = c[r];
+      } else if constexpr (T == 4) {
+        const int r32 = lane & 31, h = lane >> 5;
+        constexpr int KH = BK / 2;
+        f32x16 c;
 #pragma unroll
-      for (int q0 = 0; q0 < KH; q0 += 4) {
-        const f32x4 a = A4(as, wm0 + r32, h * KH + q0);
-        const f32x4 b = B4(bs, wn0 + r32, h * KH + q0);
+        for (int r = 0; r < 16; ++r) c[r] = acc[r];
+        static_assert(KH % 4 == 0, "whole 16-byte chunks per lane half");
 #pragma unroll
-        for (int u = 0; u < 4; ++u) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], c, 0, 0, 0);
-      }
+        for (int q0 = 0; q0 < KH; q0 += 4) {
+          const f32x4 a = A4(as, wm0 + r32, h * KH + q0);
+          const f32x4 b = B4(bs, wn0 + r32, h * KH + q0);
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[r] = c[r];
-    } else {
-      const int r32 = lane & 31, h = lane >> 5;
-      constexpr int KH = BK / 2;
-      f32x16 c00, c01, c10, c11;
+          for (int u = 0; u < 4; ++u) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], c, 0, 0, 0);
+        }
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        c00[r] = acc[r]; c01[r] = acc[16 + r]; c10[r] = acc[32 + r]; c11[r] = acc[48 + r];
-      }
-      static_assert(KH % 4 == 0, "whole 16-byte chunks per lane half");
+        for (int r = 0; r < 16; ++r) acc[r] = c[r];
+      } else {
+        const int r32 = lane & 31, h = lane >> 5;
+        constexpr int KH = BK / 2;
+        f32x16 c00, c01, c10, c11;
 #pragma unroll
-      for (int q0 = 0; q0 < KH; q0 += 4) {
-        const int k = h * KH + q0;
-        const f32x4 a0 = A4(as, wm0 + r32, k), a1 = A4(as, wm0 + 32 + r32, k);
-        const f32x4 b0 = B4(bs, wn0 + r32, k), b1 = B4(bs, wn0 + 32 + r32, k);
+        for (int r = 0; r < 16; ++r) {
+          c00[r] = acc[r]; c01[r] = acc[16 + r]; c10[r] = acc[32 + r]; c11[r] = acc[48 + r];
+        }
+        static_assert(KH % 4 == 0, "whole 16-byte chunks per lane half");
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          c00 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b0[u], c00, 0, 0, 0);
-          c01 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b1[u], c01, 0, 0, 0);
-          c10 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b0[u], c10, 0, 0, 0);
-          c11 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b1[u], c11, 0, 0, 0);
+        for (int q0 = 0; q0 < KH; q0 += 4) {
+          const int k = h * KH + q0;
+          const f32x4 a0 = A4(as, wm0 + r32, k), a1 = A4(as, wm0 + 32 + r32, k);
+          const f32x4 b0 = B4(bs, wn0 + r32, k), b1 = B4(bs, wn0 + 32 + r32, k);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            c00 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b0[u], c00, 0, 0, 0);
+            c01 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b1[u], c01, 0, 0, 0);
+            c10 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b0[u], c10, 0, 0, 0);
+            c11 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b1[u], c11, 0, 0, 0);
+          }
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          acc[r] = c00[r]; acc[16 + r] = c01[r]; acc[32 + r] = c10[r]; acc[48 + r] = c11[r];
         }
       }
+    }
+    if constexpr (T == 2) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        acc[r] = c00[r]; acc[16 + r] = c01[r]; acc[32 + r] = c10[r]; acc[48 + r] = c11[r];
+      for (int r = 0; r < 4; ++r) {
+        total[r] += acc[r];
+        acc[r] = 0.f;
       }
     }
   }
@@ -490,7 +511,7 @@ gemm_f32_dma_kernel(GemmArgs args) {
     put_blocks(sacc);
   } else if constexpr (T == 2) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r) put((lane >> 4) * 4 + r, lane & 15, acc[r]);
+    for (int r = 0; r < 4; ++r) put((lane >> 4) * 4 + r, lane & 15, total[r]);
   } else if constexpr (T == 4) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) put((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), lane & 31, acc[r]);

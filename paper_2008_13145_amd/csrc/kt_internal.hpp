@@ -120,6 +120,8 @@ constexpr size_t SPLIT_PLANE_CAP = (size_t)256 << 20;
 // Bytes of partial planes kernel `id` uses on shape s (0 when it runs unsplit
 // with an unlimited workspace).
 size_t kernel_plane_bytes(const Ctx* h, int dtype, const kt_shape* s, int32_t id);
+// Slices of K for a plain kernel that the selector picked (1: unsplit).
+int32_t deep_slices(const Ctx* h, int dtype, const kt_shape* s, int32_t id);
 // The same for a slice count (no handle needed).
 size_t split_plane_bytes(const kt_shape* s, int32_t slices);
 

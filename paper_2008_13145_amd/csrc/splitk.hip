@@ -130,6 +130,24 @@ size_t split_plane_bytes(const kt_shape* s, int32_t slices) {
   return need <= SPLIT_PLANE_CAP ? need : 0;
 }
 
+// Slices for a configuration the selector picked (no split-K variant) on a
+// deep product that leaves the chip idle.  Selection knows only the deployed
+// kernels, and a pruned set need not hold a split-K variant; one tile per
+// work-group then walks all of K alone: with (32, 32, 2, 64), 20 us at K = 2048
+// and 38 us at K = 4000 whatever M and N, against 12 and 18 us in 8 slices.
+// The line lies where two launches and the partial sums cost what the shorter
+// walk saves: K = 1024 loses 5 to 15 %, K = 1500 gains 5 to 15 %; up to 128 tiles
+// slices gain (1 x 4096 x 25088: 219 -> 80 us in 4), at 160 in 4 still 10 to 25 %
+// at K >= 2048 but lose at 1500, at 252 they gain nothing.
+int32_t deep_slices(const Ctx* h, int dtype, const kt_shape* s, int32_t id) {
+  constexpr int64_t MIN_K = 1536, MAX_TILES = 128, WORK_GROUPS = 512;
+  if (dtype != KT_F32 || s->batch != 1 || s->K < MIN_K || kernel_slices(h, dtype, id) != 1) return 1;
+  const ConfigDef& c = h->configs[dtype][id];
+  const int64_t tiles = cdiv(s->M, c.bm) * cdiv(s->N, c.bn);
+  if (tiles < 1 || tiles > MAX_TILES) return 1;
+  return tiles * 8 <= WORK_GROUPS ? 8 : 4;
+}
+
 size_t kernel_plane_bytes(const Ctx* h, int dtype, const kt_shape* s, int32_t id) {
   return split_plane_bytes(s, kernel_slices(h, dtype, id));
 }
