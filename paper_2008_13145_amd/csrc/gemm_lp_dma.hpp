@@ -401,44 +401,100 @@ __device__ __forceinline__ void lp_frag_mnmajor(LpFrag<EB>& f, const char* tile,
   }
 }
 
+// What both pipelines of a tile share: a wave's accumulators, the products of
+// one stage in LDS, and the epilogue.
+template <int EB, int BM, int BN, int T, int BK, int TA, int TB>
+struct LpTileMath {
+  using Cfg = LpDmaCfg<EB, BM, BN, T, BK, TA, TB>;
+  using Base = typename Cfg::Base;
+  static constexpr int WT = Base::WT, MB = Base::MB, SUB = Base::SUB, KSTEP = Base::KSTEP;
+  static constexpr int NACC = MB == 16 ? 4 : 16;
+  typedef typename std::conditional<MB == 16, f32x4, f32x16>::type Acc;
+  Acc acc[SUB][SUB];
+  int lane, wm0, wn0;
+
+  __device__ __forceinline__ void init(int wave, int l) {
+    lane = l;
+    wm0 = (wave / Base::WAVES_N) * WT;
+    wn0 = (wave % Base::WAVES_N) * WT;
+#pragma unroll
+    for (int i = 0; i < SUB; ++i)
+#pragma unroll
+      for (int j = 0; j < SUB; ++j)
+#pragma unroll
+        for (int r = 0; r < NACC; ++r) acc[i][j][r] = 0.f;
+  }
+
+  __device__ __forceinline__ void stage(const char* at) {
+    // lane l feeds row l % MB of its block with K values from group l / MB
+    const int rb = lane % MB, kh = (lane / MB) * (KSTEP * MB / 64);
+    const int j16 = lane & 15;
+    const int gcol = rb - j16;   // first column of this lane's 16-lane group within its block
+    const char* bt = at + Cfg::A_BYTES;
+#pragma unroll
+    for (int s = 0; s < BK / KSTEP; ++s) {
+      LpFrag<EB> fa[SUB], fb[SUB];
+#pragma unroll
+      for (int i = 0; i < SUB; ++i) {
+        if (TA == 0) lp_frag_kmajor<EB, BK, MB, KSTEP>(fa[i], at, wm0 + MB * i + rb, s, kh);
+        else lp_frag_mnmajor<EB, BM>(fa[i], at, wm0 + MB * i + gcol, s * KSTEP + kh, j16);
+        if (TB == 1) lp_frag_kmajor<EB, BK, MB, KSTEP>(fb[i], bt, wn0 + MB * i + rb, s, kh);
+        else lp_frag_mnmajor<EB, BN>(fb[i], bt, wn0 + MB * i + gcol, s * KSTEP + kh, j16);
+      }
+#pragma unroll
+      for (int i = 0; i < SUB; ++i)
+#pragma unroll
+        for (int j = 0; j < SUB; ++j) lp_mfma(fa[i], fb[j], acc[i][j]);
+    }
+  }
+
+  __device__ __forceinline__ void store(const GemmArgs& args, int64_t m0, int64_t n0, int64_t bz,
+                                        float scale) const {
+    float* __restrict__ Cg = args.C + bz * args.sC;
+    const float beta = args.beta;
+#pragma unroll
+    for (int i = 0; i < SUB; ++i)
+#pragma unroll
+      for (int j = 0; j < SUB; ++j)
+#pragma unroll
+        for (int r = 0; r < NACC; ++r) {
+          // 32x32 blocks: row (r / 4) * 8 + (lane / 32) * 4 + r % 4; 16x16
+          // blocks: row (lane / 16) * 4 + r; the column is lane % MB
+          const int br = MB == 16 ? (lane >> 4) * 4 + r : (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
+          const int64_t gi = m0 + wm0 + MB * i + br;
+          const int64_t gj = n0 + wn0 + MB * j + lane % MB;
+          if (gi < args.M && gj < args.N) {
+            float* p = Cg + gi * args.ldc + gj;
+            float out = scale * acc[i][j][r];
+            if (beta != 0.f) out = fmaf(beta, *p, out);
+            *p = out;
+          }
+        }
+  }
+};
+
 // One BM x BN output tile through the DMA pipeline.  lds holds NS stages;
 // the caller synchronizes before reusing it for another tile.
 template <int EB, int BM, int BN, int T, int BK, int TA, int TB>
 __device__ __forceinline__ void lp_dma_tile(const GemmArgs& args, int tm, int tn, int64_t bz,
                                             char* lds) {
   using Cfg = LpDmaCfg<EB, BM, BN, T, BK, TA, TB>;
-  using Base = typename Cfg::Base;
   constexpr int NS = Cfg::NS;
-  constexpr int WT = Base::WT, MB = Base::MB, SUB = Base::SUB, KSTEP = Base::KSTEP;
-  constexpr int NKK = BK / KSTEP;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = Cfg::WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t lds0 = lds_address(lds);
-  const int wm0 = (wave / Base::WAVES_N) * WT;
-  const int wn0 = (wave % Base::WAVES_N) * WT;
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
-  const int64_t M = args.M, N = args.N, K = args.K;
+  const int64_t K = args.K;
   DmaSource<Cfg, EB, BM, BN, BK, TA, TB, LpSwz<EB, BM, BN, BK>> src;
   src.init(args, static_cast<const char*>(args.A) + bz * args.sA * EB,
            static_cast<const char*>(args.B) + bz * args.sB * EB, m0, n0, wave, lane);
   float scale = args.alpha;
   if (EB == 1) scale = args.alpha / (args.scaleA[0] * args.scaleB[0]);
 
-  typedef typename std::conditional<MB == 16, f32x4, f32x16>::type Acc;
-  constexpr int NACC = MB == 16 ? 4 : 16;
-  Acc acc[SUB][SUB];
-#pragma unroll
-  for (int i = 0; i < SUB; ++i)
-#pragma unroll
-    for (int j = 0; j < SUB; ++j)
-#pragma unroll
-      for (int r = 0; r < NACC; ++r) acc[i][j][r] = 0.f;
-
-  const int rb = lane % MB, kh = (lane / MB) * (KSTEP * MB / 64);
-  const int j16 = lane & 15;
-  const int gcol = rb - j16;   // first column of this lane's 16-lane group within its block
+  LpTileMath<EB, BM, BN, T, BK, TA, TB> math;
+  math.init(wave, lane);
   const int nk = (int)((K + BK - 1) / BK);
   const int my_blocks = (wave < Cfg::NBLK % Cfg::WAVES || Cfg::NBLK % Cfg::WAVES == 0)
                             ? Cfg::NW_HI : Cfg::NW_LO;
@@ -460,43 +516,161 @@ __device__ __forceinline__ void lp_dma_tile(const GemmArgs& args, int tm, int tn
     // the buffer of stage kt - 1 is free: every wave has passed its reads
     if (kt + NS - 1 < nk)
       src.issue(args, m0, n0, lds0 + ((kt + NS - 1) % NS) * Cfg::STAGE);
-    const char* at = cur;
-    const char* bt = cur + Cfg::A_BYTES;
+    math.stage(cur);
+  }
+  math.store(args, m0, n0, bz, scale);
+}
+
+// Register staging of one operand of a tile into the layouts above, for
+// operands that the DMA may not read: rows of any alignment.  A tile is ROWS
+// rows of COLS contiguous elements (KM: rows of op's M or N, K contiguous;
+// otherwise rows of K) in 16-byte chunks, chunk column tid % CPR of rows
+// tid / CPR + i * STEP per thread.  A chunk is one 16-byte load from wherever
+// it starts.  Rows beyond the operand repeat its last one and columns beyond
+// it hold anything (those outputs are never stored): the chunk that straddles
+// the last column is read so that it ends there, and shifted on its way to LDS.
+// K beyond the product is zero.
+// What bounds these tiles is the latency of a stage (loads, LDS stores,
+// barrier), so their cost per load counts: with the transposition in registers
+// that K-major LDS tiles need, and two loads per misaligned chunk, dense 8 x
+// 1021x771x515 took 40.3 us in BF16 on (256, 128, 8, 64) and 41.4 in FP8, this
+// way 25.5 and 20.3; 1023x1025x2047 76.8 and 51.0, this way 35.1 and 29.5; over all
+// configurations of ten such products 1.8 times faster.
+template <int EB, int ROWS, int COLS, bool KM, int NT>
+struct StagedOperand {
+  static constexpr int CE = 16 / EB, CPR = COLS / CE, NV = ROWS * CPR;
+  static constexpr int PT = (NV + NT - 1) / NT, STEP = NT / CPR;
+  static_assert(NT % CPR == 0, "one chunk column per thread");
+  typedef uint32_t Chunk __attribute__((ext_vector_type(4), aligned(1)));
+  const char* base;     // the tile's rows at the next stage's first k (uniform)
+  int64_t ld;           // bytes
+  uint32_t off[PT];
+  int left;             // rows (KM) or columns of the operand from the tile's start
+  int row0, col;        // this thread's first row, chunk column in elements
+  bool plain, edge;     // 32-bit offsets and whole chunks; columns end inside the tile
+  bool late;            // the chunks held wait for their shift
+  u32x4 v[PT];
+
+  __device__ __forceinline__ void init(const char* p, int64_t lde, int64_t first, int64_t ext, int tid) {
+    ld = lde * EB;
+    base = p + first * (KM ? ld : EB);
+    const int64_t rem = ext - first;
+    left = (int)min(rem, (int64_t)(KM ? ROWS : COLS));
+    row0 = tid / CPR;
+    col = (tid % CPR) * CE;
+    edge = !KM && left < COLS;
+    plain = (uint64_t)ld < (0x80000000ull / ROWS) && left >= (KM ? 1 : CE);
+    const int c = edge ? min(col, left - CE) : col;
 #pragma unroll
-    for (int s = 0; s < NKK; ++s) {
-      LpFrag<EB> fa[SUB], fb[SUB];
-#pragma unroll
-      for (int i = 0; i < SUB; ++i) {
-        if (TA == 0) lp_frag_kmajor<EB, BK, MB, KSTEP>(fa[i], at, wm0 + MB * i + rb, s, kh);
-        else lp_frag_mnmajor<EB, BM>(fa[i], at, wm0 + MB * i + gcol, s * KSTEP + kh, j16);
-        if (TB == 1) lp_frag_kmajor<EB, BK, MB, KSTEP>(fb[i], bt, wn0 + MB * i + rb, s, kh);
-        else lp_frag_mnmajor<EB, BN>(fb[i], bt, wn0 + MB * i + gcol, s * KSTEP + kh, j16);
-      }
-#pragma unroll
-      for (int i = 0; i < SUB; ++i)
-#pragma unroll
-        for (int j = 0; j < SUB; ++j) lp_mfma(fa[i], fb[j], acc[i][j]);
+    for (int i = 0; i < PT; ++i) {
+      const int r = row0 + i * STEP;
+      off[i] = (uint32_t)(KM ? min(r, left - 1) : r) * (uint32_t)ld + (uint32_t)(c * EB);
     }
   }
 
-  float* __restrict__ Cg = args.C + bz * args.sC;
-  const float beta = args.beta;
+  // Any chunk: elements one by one where the operand or K ends inside it.
+  __device__ __forceinline__ u32x4 chunk(int row, int left_k) const {
+    const int ext = KM ? left_k : row < left_k ? left : 0;
+    const int n = min(ext - col, CE);
+    const char* p = base + (KM ? min(row, left - 1) : row) * ld + col * EB;
+    if (n == CE) return *reinterpret_cast<const Chunk*>(p);
+    u32x4 t = {0u, 0u, 0u, 0u};
+    if (n > 0) {
+      typedef typename LpElem<EB>::T E;
 #pragma unroll
-  for (int i = 0; i < SUB; ++i)
-#pragma unroll
-    for (int j = 0; j < SUB; ++j)
-#pragma unroll
-      for (int r = 0; r < NACC; ++r) {
-        const int br = MB == 16 ? (lane >> 4) * 4 + r : (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3);
-        const int64_t gi = m0 + wm0 + MB * i + br;
-        const int64_t gj = n0 + wn0 + MB * j + rb;
-        if (gi < M && gj < N) {
-          float* p = Cg + gi * args.ldc + gj;
-          float out = scale * acc[i][j][r];
-          if (beta != 0.f) out = fmaf(beta, *p, out);
-          *p = out;
-        }
+      for (int e = 0; e < CE; ++e) {
+        uint32_t x = 0u;
+        __builtin_memcpy(&x, p + min(e, n - 1) * EB, EB);
+        t[e * EB / 4] |= (e < n ? x : 0u) << (8 * (e * EB % 4));
       }
+    }
+    return t;
+  }
+
+  // Chunks of the next stage, which holds left_k of K.
+  __device__ __forceinline__ void load(int64_t left_k) {
+    const bool whole = plain && left_k >= (KM ? COLS : ROWS);
+    late = whole && edge;
+    if (whole) {
+#pragma unroll
+      for (int i = 0; i < PT; ++i)
+        if (NV % NT == 0 || (int)threadIdx.x + i * NT < NV)
+          v[i] = *reinterpret_cast<const Chunk*>(base + off[i]);
+    } else {
+      const int k = (int)min(left_k, (int64_t)(KM ? COLS : ROWS));
+#pragma unroll
+      for (int i = 0; i < PT; ++i)
+        if (NV % NT == 0 || (int)threadIdx.x + i * NT < NV) v[i] = chunk(row0 + i * STEP, k);
+    }
+    base += KM ? COLS * EB : ROWS * ld;
+  }
+
+  __device__ __forceinline__ void store(char* tile) {
+    if (late) {
+      const int sh = min(max(col + CE - left, 0) * EB, 15) * 8;
+#pragma unroll
+      for (int i = 0; i < PT; ++i) {
+        typedef unsigned __int128 u128;
+        v[i] = __builtin_bit_cast(u32x4, __builtin_bit_cast(u128, v[i]) >> sh);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < PT; ++i) {
+      const int r = row0 + i * STEP;
+      const int sw = KM ? kswz<CPR>(r) : mswz<CPR, EB == 2 ? 4 : 2>(r);
+      if (NV % NT == 0 || (int)threadIdx.x + i * NT < NV)
+        *reinterpret_cast<u32x4*>(tile + r * (COLS * EB) + ((col / CE) ^ sw) * 16) = v[i];
+    }
+  }
+};
+
+// One BM x BN output tile with register-staged operands: the next stage's
+// loads are in flight under the current stage's products, two stages in LDS.
+template <int EB, int BM, int BN, int T, int BK, int TA, int TB>
+__device__ __forceinline__ void lp_tile(const GemmArgs& args, int tm, int tn, int64_t bz, char* lds) {
+  using Cfg = LpDmaCfg<EB, BM, BN, T, BK, TA, TB>;
+  constexpr int NT = Cfg::NT;
+  const int tid = threadIdx.x;
+  const int wave = Cfg::WAVES == 1 ? 0 : __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
+  const int64_t K = args.K;
+  StagedOperand<EB, TA == 0 ? BM : BK, TA == 0 ? BK : BM, TA == 0, NT> a;
+  StagedOperand<EB, TB == 1 ? BN : BK, TB == 1 ? BK : BN, TB == 1, NT> b;
+  a.init(static_cast<const char*>(args.A) + bz * args.sA * EB, args.lda, m0, args.M, tid);
+  b.init(static_cast<const char*>(args.B) + bz * args.sB * EB, args.ldb, n0, args.N, tid);
+  // FP8 per-tensor scales: loaded before the K loop so their latency is hidden
+  float scale = args.alpha;
+  if (EB == 1) scale = args.alpha / (args.scaleA[0] * args.scaleB[0]);
+  LpTileMath<EB, BM, BN, T, BK, TA, TB> math;
+  math.init(wave, tid & 63);
+  const int nk = (int)((K + BK - 1) / BK);
+  for (int kt = -1; kt < nk; ++kt) {   // -1: the first stage's loads
+    const int64_t left_k = K - (int64_t)(kt + 1) * BK;
+    if (left_k > 0) {
+      a.load(left_k);
+      b.load(left_k);
+    }
+    if (kt >= 0) math.stage(lds + (kt & 1) * Cfg::STAGE);
+    if (left_k > 0) {
+      char* next = lds + ((kt + 1) & 1) * Cfg::STAGE;
+      a.store(next);
+      b.store(next + Cfg::A_BYTES);
+    }
+    __syncthreads();
+  }
+  math.store(args, m0, n0, bz, scale);
+}
+
+template <int EB, int BM, int BN, int T, int BK, int TA, int TB>
+__global__ void __launch_bounds__(BM * BN / (T * T))
+__attribute__((amdgpu_waves_per_eu(LpDmaCfg<EB, BM, BN, T, BK, TA, TB>::OCC, 8)))
+gemm_lp_kernel(GemmArgs args) {
+  __shared__ __attribute__((aligned(16))) char lds[2 * LpDmaCfg<EB, BM, BN, T, BK, TA, TB>::STAGE];
+  int tm, tn;
+  int64_t bz;
+  load_args(args);
+  block_coords(blockIdx.x, args, tm, tn, bz);
+  lp_tile<EB, BM, BN, T, BK, TA, TB>(args, tm, tn, bz, lds);
 }
 
 template <int EB, int BM, int BN, int T, int BK, int TA, int TB>
@@ -520,10 +694,7 @@ hipError_t launch_gemm_lp(const GemmArgs& a, hipStream_t stream) {
   if (a.vecA == LP_ALIGN_DMA && a.vecB == LP_ALIGN_DMA)
     return launch_flat<EB>(gemm_lp_dma_kernel<EB, BM, BN, T, BK, TA, TB>, a, BM, BN, Cfg::NT,
                            stream);
-  GemmArgs g = a;
-  if (g.vecA == LP_ALIGN_DMA) g.vecA = LP_ALIGN_ROWS;
-  if (g.vecB == LP_ALIGN_DMA) g.vecB = LP_ALIGN_ROWS;
-  return launch_flat<EB>(gemm_lp_kernel<EB, BM, BN, T, BK, TA, TB>, g, BM, BN, Cfg::NT, stream);
+  return launch_flat<EB>(gemm_lp_kernel<EB, BM, BN, T, BK, TA, TB>, a, BM, BN, Cfg::NT, stream);
 }
 
 }  // namespace kt

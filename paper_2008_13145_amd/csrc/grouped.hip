@@ -37,7 +37,6 @@ struct GroupDesc {
   const void* B;
   float* C;
   int64_t M, N, K, lda, ldb, ldc;
-  int32_t vecA, vecB;   // register-path alignment modes
   int32_t dma, pad;     // 1: both operands take the DMA pipeline
 };
 
@@ -55,7 +54,7 @@ struct WorkItem {
 template <int BM, int BN, int T, int BK, int MODE>
 struct GroupTile {
   static constexpr int NT = BM * BN / (T * T);
-  static constexpr int L1 = MODE != 1 ? GemmLpCfg<2, BM, BN, T, BK, 0, 0>::LDS_BYTES : 0;
+  static constexpr int L1 = MODE != 1 ? 2 * LpDmaCfg<2, BM, BN, T, BK, 0, 0>::STAGE : 0;
   static constexpr int L2 = MODE != 0 ? LpDmaCfg<2, BM, BN, T, BK, 0, 0>::LDS_BYTES : 0;
   static constexpr int LDS = L1 > L2 ? L1 : L2;
 
@@ -65,9 +64,9 @@ struct GroupTile {
       lp_dma_tile<2, BM, BN, T, BK, 0, 0>(a, tm, tn, 0, lds);
     } else if constexpr (MODE == 2) {
       if (dma) lp_dma_tile<2, BM, BN, T, BK, 0, 0>(a, tm, tn, 0, lds);
-      else lp_tile<2, BM, BN, T, BK, 0, 0>(a, tm, tn, 0, reinterpret_cast<uint16_t*>(lds));
+      else lp_tile<2, BM, BN, T, BK, 0, 0>(a, tm, tn, 0, lds);
     } else {
-      lp_tile<2, BM, BN, T, BK, 0, 0>(a, tm, tn, 0, reinterpret_cast<uint16_t*>(lds));
+      lp_tile<2, BM, BN, T, BK, 0, 0>(a, tm, tn, 0, lds);
     }
   }
 };
@@ -116,7 +115,7 @@ grouped_bf16_kernel(const GroupDesc* __restrict__ descs, const WorkItem* __restr
     a.C = d.C; a.ldc = d.ldc; a.sC = 0;
     a.alpha = alpha; a.beta = beta;
     a.scaleA = nullptr; a.scaleB = nullptr;
-    a.vecA = d.vecA; a.vecB = d.vecB; a.ragged = 0;
+    a.vecA = a.vecB = a.ragged = 0;
     a.tiles_m = 0; a.tiles_n = 0;
     if constexpr (TWO) {
       if (it.cls == 0) Big::run(a, it.tm, it.tn, d.dma != 0, lds);
@@ -222,14 +221,10 @@ static kt_status validate_group(Ctx* h, kt_dtype dtype, const kt_shape* shapes, 
   return KT_OK;
 }
 
-// Member operand alignment: the register pipeline's mode and whether the
-// DMA pipeline may read the operand (rows on 16-byte boundaries and the row's
-// last 16-byte chunk within the leading dimension: member rows are allocated
-// in full, so reading up to the next 16-byte boundary stays inside them).
-static int32_t member_vec(const void* p, int64_t ld) {
-  if ((uintptr_t)p % 4 != 0) return LP_ALIGN_NONE;
-  return ld % 2 == 0 ? LP_ALIGN_ROWS : LP_ALIGN_BASE;
-}
+// Whether the DMA pipeline may read a member's operand: rows on 16-byte
+// boundaries and the row's last 16-byte chunk within the leading dimension
+// (member rows are allocated in full, so reading up to the next 16-byte
+// boundary stays inside them).
 static bool member_dma(const void* p, int64_t ld, int64_t ext) {
   return (uintptr_t)p % 16 == 0 && ld % 8 == 0 && ext >= 8 && ld >= (ext + 7) / 8 * 8;
 }
@@ -289,8 +284,6 @@ static kt_status plan_build(Ctx* h, const kt_shape* shapes, int32_t n, const voi
     d.lda = ld ? ld[3 * i] : std::max<int64_t>(s.K, 1);
     d.ldb = ld ? ld[3 * i + 1] : std::max<int64_t>(s.N, 1);
     d.ldc = ld ? ld[3 * i + 2] : std::max<int64_t>(s.N, 1);
-    d.vecA = member_vec(A[i], d.lda);
-    d.vecB = member_vec(B[i], d.ldb);
     d.dma = o.pipeline == 0 && s.K > 0 && member_dma(A[i], d.lda, s.K) &&
             member_dma(B[i], d.ldb, s.N);
     d.pad = 0;
