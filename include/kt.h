@@ -193,8 +193,9 @@ kt_status kt_gemm(kt_handle h, kt_dtype in_dtype, const kt_shape* s, float alpha
  * whose A and B tiles are whole KiB (bm * bk, bn * bk multiples of 256) have
  * the DMA pipeline; it sums K in another order than the register-staged one
  * (results within the same bound, not bit-identical) and also takes rows on
- * 4-byte boundaries, for which *dma is 0, when K and the contiguous extents
- * are at least 4; the other configurations always run register-staged. */
+ * 4-byte boundaries, for which *dma is 0, when K fills its stages (256 for
+ * t = 2, 3 bk otherwise) and the contiguous extents are at least 4; the other
+ * configurations always run register-staged. */
 kt_status kt_dma_pipeline(kt_handle h, kt_dtype dtype, const kt_shape* s, const void* A,
                          int64_t lda, int64_t strideA, const void* B, int64_t ldb, int64_t strideB,
                          int32_t* dma);

@@ -73,14 +73,19 @@ __device__ __forceinline__ void f32_dma_zero_tail(char* stage, int kvalid, int t
     const bool kmajor = op == 0 ? (TA == 0) : (TB == 1);
     const int cols = op == 0 ? BM : BN;
     float* t = reinterpret_cast<float*>(stage + (op == 0 ? 0 : Cfg::A_BYTES));
-    const int tail = BK - kvalid;
     if (kmajor) {
-      for (int i = tid; i < cols * tail; i += Cfg::NT) {
-        const int r = i / tail, k = kvalid + i % tail;
-        t[r * BK + ((k >> 2) ^ kswz<Cfg::KCPR>(r)) * 4 + (k & 3)] = 0.f;
+      constexpr int CPR = Cfg::KCPR;
+      for (int i = tid; i < cols * CPR; i += Cfg::NT) {
+        const int r = i / CPR, c = i % CPR;
+        f32x4* p = reinterpret_cast<f32x4*>(t + r * BK) + (c ^ kswz<CPR>(r));
+        const int from = kvalid - 4 * c;   // first element to clear
+        if (from <= 0) *p = f32x4{0.f, 0.f, 0.f, 0.f};
+        else
+          for (int e = from; e < 4; ++e) (*p)[e] = 0.f;
       }
     } else {
-      for (int i = tid; i < cols * tail; i += Cfg::NT) t[kvalid * cols + i] = 0.f;
+      for (int i = kvalid * cols / 4 + tid; i < BK * cols / 4; i += Cfg::NT)
+        reinterpret_cast<f32x4*>(t)[i] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
   }
 }
@@ -543,6 +548,17 @@ struct F32DmaServes {
 // (DmaSource::settle).  Any other operand takes the register-staged kernel.
 // Dense 1001x1003x1005 NN: (32, 32, 2, 32) 37.5 -> 28.1 us, (64, 64, 4, 32)
 // 45.9 -> 33.0 us, (128, 128, 8, 16) 134 -> 57 us (the last on the split kernel).
+// Such rows need a K that fills the stages: a shallow product has no use for
+// their LDS, which costs it resident work-groups, and its last stage takes a
+// pass more.  8 x 500x500 dense: on (32, 32, 2, 64) register-staged / DMA 14.6 / 19.7
+// us at K = 65, 18.8 / 23.0 at 129, 9.2 / 7.5 at 257 (4 x 250x251); on (64, 64, 4, 16)
+// 7.8 / 8.0 at 33, 9.8 / 9.4 at 65, 13.9 / 12.2 at 129; on (128, 64, 4, 32) 10.1 /
+// 10.2 at 65, 13.7 / 13.0 at 129.
+template <int T, int BK>
+struct F32DenseK {
+  static constexpr int value = T == 2 ? 256 : 3 * BK;
+};
+
 template <int BM, int BN, int T, int BK, int TA, int TB>
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t stream) {
   using Cfg = GemmF32Cfg<BM, BN, T, BK, TA, TB>;
@@ -551,7 +567,8 @@ hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t stream) {
         (TA == 0 || a.M >= 4) && (TB == 1 || a.N >= 4)) {
       GemmArgs g = a;
       g.ragged = a.vecA != LP_ALIGN_DMA || a.vecB != LP_ALIGN_DMA;
-      return launch_flat<4>(gemm_f32_dma_kernel<BM, BN, T, BK, TA, TB>, g, BM, BN, Cfg::NT, stream);
+      if (!g.ragged || a.K >= F32DenseK<T, BK>::value)
+        return launch_flat<4>(gemm_f32_dma_kernel<BM, BN, T, BK, TA, TB>, g, BM, BN, Cfg::NT, stream);
     }
   }
   return launch_flat<4>(gemm_f32_kernel<BM, BN, T, BK, TA, TB>, a, BM, BN, Cfg::NT, stream);

@@ -198,14 +198,14 @@ struct DmaSource {
     return i * Cfg::WAVES < Cfg::NBA && wave + i * Cfg::WAVES < Cfg::NBA;
   }
 
-  // Offsets of block i beyond K in the last stage, moved back to its last
-  // chunk or row.
-  __device__ __forceinline__ uint32_t in_tail(const GemmArgs& g, int i) const {
+  // Offsets of block i beyond K in the last stage, which holds left_k of it, moved
+  // back to its last chunk or row.
+  __device__ __forceinline__ uint32_t in_tail(const GemmArgs& g, int i, int left_k) const {
     bool is_a, kmajor;
     int r, col;
     place(wave + i * Cfg::WAVES, lane, is_a, kmajor, r, col);
-    if (kmajor) return off[i] - (uint32_t)max(col - (tail - 1) / CE * CE, 0) * EB;
-    return off[i] - (uint32_t)max(r - (tail - 1), 0) * (uint32_t)((is_a ? g.lda : g.ldb) * EB);
+    if (kmajor) return off[i] - (uint32_t)max(col - (left_k - 1) / CE * CE, 0) * EB;
+    return off[i] - (uint32_t)max(r - (left_k - 1), 0) * (uint32_t)((is_a ? g.lda : g.ldb) * EB);
   }
 
   __device__ __forceinline__ void init(const GemmArgs& g, const char* Ag, const char* Bg,
@@ -240,11 +240,29 @@ struct DmaSource {
     }
   }
 
+  // Offsets, in the last stage, of the last 16 bytes of A and B where the tile
+  // holds them: the only chunk of the operand that starts later is the one that
+  // runs over its end.  False when they start before the tile.
+  __device__ __forceinline__ bool ends(const GemmArgs& g, int64_t m0, int64_t n0, int left_k,
+                                       uint32_t& ea, uint32_t& eb) const {
+    const uint64_t over_m = (uint64_t)(g.M - m0), over_n = (uint64_t)(g.N - n0);
+    const int left_m = (over_m >> 31) ? BM + 1 : min(BM + 1, (int)over_m);
+    const int left_n = (over_n >> 31) ? BN + 1 : min(BN + 1, (int)over_n);
+    const int lda = (int)g.lda, ldb = (int)g.ldb;
+    const int la = (TA == 0 ? (left_m - 1) * lda + left_k : (left_k - 1) * lda + left_m) - CE;
+    const int lb = (TB == 1 ? (left_n - 1) * ldb + left_k : (left_k - 1) * ldb + left_n) - CE;
+    ea = left_m <= BM ? (uint32_t)la * EB : ~0u;
+    eb = left_n <= BN ? (uint32_t)lb * EB : ~0u;
+    return (left_m > BM || la >= 0) && (left_n > BN || lb >= 0);
+  }
+
   // Issue the next stage into the LDS at byte address `stage`.
   __device__ __forceinline__ void issue(const GemmArgs& g, int64_t m0, int64_t n0, uint32_t stage) {
-    const bool last = whole <= (tail == 0 ? 1 : 0);
-    if (offsets && !(ragged && last)) {
-      if (whole > 0) {
+    const bool last = whole <= (tail == 0 ? 1 : 0), end = ragged && last;
+    const int left_k = whole > 0 ? BK : tail;
+    uint32_t ea = ~0u, eb = ~0u;
+    if (offsets && (!end || ends(g, m0, n0, left_k, ea, eb))) {
+      if (whole > 0 && !end) {
 #pragma unroll
         for (int i = 0; i < Cfg::NW_HI; ++i)
           if (exists(i))
@@ -253,12 +271,12 @@ struct DmaSource {
 #pragma unroll
         for (int i = 0; i < Cfg::NW_HI; ++i)
           if (exists(i))
-            lds_dma16(of_a(i) ? a : b, in_tail(g, i), stage + (wave + i * Cfg::WAVES) * 1024);
+            lds_dma16(of_a(i) ? a : b,
+                      EB == 4 ? min(in_tail(g, i, left_k), of_a(i) ? ea : eb) : in_tail(g, i, left_k),
+                      stage + (wave + i * Cfg::WAVES) * 1024);
       }
     } else {
-      // whole addresses: a loop, out of the way of the products that have
-      // offsets; the last stage of a ragged product
-      const int left_k = whole > 0 ? BK : tail;
+      // whole addresses: a loop, out of the way of the products that have offsets
 #pragma nounroll
       for (int q = wave; q < Cfg::NBLK; q += Cfg::WAVES) {
         bool is_a, kmajor;
@@ -327,16 +345,20 @@ __device__ __forceinline__ void lp_dma_zero_tail(char* stage, int kvalid, int ti
     const bool kmajor = op == 0 ? (TA == 0) : (TB == 1);
     const int rows_c = op == 0 ? BM : BN;
     E* t = reinterpret_cast<E*>(stage + (op == 0 ? 0 : Cfg::A_BYTES));
-    const int tail = BK - kvalid;
     if (kmajor) {
       constexpr int CPR = BK * EB / 16, CE = 16 / EB;
-      for (int i = tid; i < rows_c * tail; i += Cfg::NT) {
-        const int r = i / tail, k = kvalid + i % tail;
-        const int c = k / CE, w = k % CE;
-        t[r * BK + (c ^ kswz<CPR>(r)) * CE + w] = (E)0;
+      for (int i = tid; i < rows_c * CPR; i += Cfg::NT) {
+        const int r = i / CPR, c = i % CPR;
+        E* p = t + r * BK + (c ^ kswz<CPR>(r)) * CE;
+        const int from = kvalid - CE * c;   // first element to clear
+        if (from <= 0) *reinterpret_cast<u32x4*>(p) = u32x4{0u, 0u, 0u, 0u};
+        else
+          for (int e = from; e < CE; ++e) p[e] = (E)0;
       }
     } else {
-      for (int i = tid; i < rows_c * tail; i += Cfg::NT) t[kvalid * rows_c + i] = (E)0;
+      const int per = rows_c * EB / 16;   // chunks per row
+      for (int i = kvalid * per + tid; i < BK * per; i += Cfg::NT)
+        reinterpret_cast<u32x4*>(t)[i] = u32x4{0u, 0u, 0u, 0u};
     }
   }
 }
