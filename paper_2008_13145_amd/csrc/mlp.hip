@@ -137,14 +137,18 @@ __global__ void mlp_targets_kernel(const uint16_t* __restrict__ Xq, int n, int d
 // from a register lane by lane, so LDS carries one word per activation instead
 // of two per multiply.  Every sum runs in the order r or i = 0, 1, ... of its
 // block, one fused multiply-add each.  What bounds it is the chain of dependent
-// phases of one step, not the chip: 3000 steps of 960 rows take 71.6 ms, with one
-// work-group per block that read both factors of every multiply from LDS 113 ms.
+// phases of one step, not the chip (of 26 k clocks, 9.6 k wait for the scalar loads
+// of W2, 6.6 k are the products over rows): so sixteen waves, two per unit of the
+// slice with one row block each.  3000 steps of 960 rows: 60 ms; eight waves that take
+// both blocks 71; one work-group per block that read both factors of every
+// multiply from LDS 113.
 static constexpr int MLP_SLICES = 8;
-static constexpr int MLP_WAVES = 8;
+static constexpr int MLP_WAVES = 16;
+static constexpr int MLP_OUT_WAVES = 8;                // waves that share the last layer's outputs
 static constexpr int MLP_GRAD_THREADS = MLP_WAVES * 64;
 static constexpr int MLP_UNITS = MLP_H / MLP_WAVES;    // units of a layer per wave
 static constexpr int MLP_LD = 65;                      // LDS row: 64 rows of the batch, odd stride
-static_assert(MLP_H / MLP_SLICES == MLP_WAVES, "one unit of a slice per wave");
+static_assert(2 * MLP_H / MLP_SLICES == MLP_WAVES, "one unit of a slice and one row block per wave");
 
 __global__ void __launch_bounds__(MLP_GRAD_THREADS)
 mlp_fwdbwd_kernel(const float* __restrict__ P, const float* __restrict__ X, const float* __restrict__ Y,
@@ -155,8 +159,7 @@ mlp_fwdbwd_kernel(const float* __restrict__ P, const float* __restrict__ X, cons
   float* Z1 = sm;                               // [unit][row], before the ReLU
   float* Z2 = Z1 + MLP_H * MLP_LD;
   float* D2 = Z2 + MLP_H * MLP_LD;              // dz2
-  float* D1 = D2 + MLP_H * MLP_LD;              // [wave][row]: dz1 of the slice's units
-  float* XS = D1 + MLP_WAVES * MLP_LD;          // [row][6]
+  float* XS = D2 + MLP_H * MLP_LD;              // [row][6]
   float* DY = XS + 2 * MLP_ROWS * MLP_IN;       // [output][row]
   __shared__ float red[MLP_WAVES][2];
   const int tid = threadIdx.x, lane = tid & 63;
@@ -201,7 +204,7 @@ mlp_fwdbwd_kernel(const float* __restrict__ P, const float* __restrict__ X, cons
   for (int i = 0; i < MLP_H; ++i) h[i] = fmaxf(Z2[i * MLP_LD + lane], 0.f);
   const float scale = 2.0f / ((float)n * (float)k);
   float lsum = 0.f;
-  for (int o = wave; o < k; o += MLP_WAVES) {
+  for (int o = wave; wave < MLP_OUT_WAVES && o < k; o += MLP_OUT_WAVES) {
     const float* w = P + L.oW3 + o * MLP_H;
     float s = P[L.ob3 + o];
 #pragma unroll
@@ -224,7 +227,7 @@ mlp_fwdbwd_kernel(const float* __restrict__ P, const float* __restrict__ X, cons
   __syncthreads();
   if (slice == 0 && tid < 2 && r0 + tid * MLP_ROWS < n) {
     float s = 0.f;
-    for (int w = 0; w < MLP_WAVES; ++w) s += red[w][tid];
+    for (int w = 0; w < MLP_OUT_WAVES; ++w) s += red[w][tid];
     part_loss[blockIdx.x * 2 + tid] = s;
   }
   // dz2 = (dy W3) * [z2 > 0]
@@ -243,8 +246,8 @@ mlp_fwdbwd_kernel(const float* __restrict__ P, const float* __restrict__ X, cons
       D2[(u0 + q) * MLP_LD + lane] = Z2[(u0 + q) * MLP_LD + lane] > 0.f ? acc[q] : 0.f;
   }
   __syncthreads();
-  // dz1 = (dz2 W2) * [z1 > 0], unit `unit` of this slice
-  const int unit = slice * MLP_WAVES + wave;
+  // dz1 = (dz2 W2) * [z1 > 0], unit `unit` of this slice (both waves of a unit)
+  const int unit = slice * (MLP_WAVES / 2) + wave / 2, half = wave % 2;
   float d1 = 0.f;
   {
     const float* w = P + L.oW2 + unit;
@@ -252,52 +255,52 @@ mlp_fwdbwd_kernel(const float* __restrict__ P, const float* __restrict__ X, cons
     for (int o = 0; o < MLP_H; ++o) d1 = fmaf(D2[o * MLP_LD + lane], w[o * MLP_H], d1);
     d1 = Z1[unit * MLP_LD + lane] > 0.f ? d1 : 0.f;
   }
-  const float d2 = D2[unit * MLP_LD + lane];
-  // products over the rows of each block: lane -> input unit, the factor of
+  // lane r (and r + 32): row r of this wave's block
+  const int mine = half * MLP_ROWS + lane % MLP_ROWS;
+  const float d2 = D2[unit * MLP_LD + mine];
+  d1 = __shfl(d1, mine);
+  // products over the rows of one block: lane -> input unit, the factor of
   // row r broadcast from lane r
   auto lane_of = [](float v, int l) {
     return __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(v), l));
   };
+  if (r0 + half * MLP_ROWS >= n) return;
+  float* g = part + (int64_t)(blockIdx.x * 2 + half) * L.total;
+  // dW2[unit][i] = sum_r dz2[r][unit] relu(z1[r][i]);  db2
+  float s = 0.f, sb = 0.f;
 #pragma unroll
-  for (int half = 0; half < 2; ++half) {
-    if (r0 + half * MLP_ROWS >= n) break;
-    float* g = part + (int64_t)(blockIdx.x * 2 + half) * L.total;
-    // dW2[unit][i] = sum_r dz2[r][unit] relu(z1[r][i]);  db2
-    float s = 0.f, sb = 0.f;
+  for (int r = 0; r < MLP_ROWS; ++r) {
+    const float v = lane_of(d2, r);
+    s = fmaf(v, fmaxf(Z1[lane * MLP_LD + half * MLP_ROWS + r], 0.f), s);
+    sb += v;
+  }
+  g[L.oW2 + unit * MLP_H + lane] = s;
+  if (lane == 0) g[L.ob2 + unit] = sb;
+  // dW1[unit][i] = sum_r dz1[r][unit] x[r][i];  db1
+  s = 0.f;
+  sb = 0.f;
+  const int i6 = lane < MLP_IN ? lane : 0;
 #pragma unroll
-    for (int r = 0; r < MLP_ROWS; ++r) {
-      const float v = lane_of(d2, half * MLP_ROWS + r);
-      s = fmaf(v, fmaxf(Z1[lane * MLP_LD + half * MLP_ROWS + r], 0.f), s);
-      sb += v;
-    }
-    g[L.oW2 + unit * MLP_H + lane] = s;
-    if (lane == 0) g[L.ob2 + unit] = sb;
-    // dW1[unit][i] = sum_r dz1[r][unit] x[r][i];  db1
+  for (int r = 0; r < MLP_ROWS; ++r) {
+    const float v = lane_of(d1, r);
+    s = fmaf(v, XS[(half * MLP_ROWS + r) * MLP_IN + i6], s);
+    sb += v;
+  }
+  if (lane < MLP_IN) g[L.oW1 + unit * MLP_IN + lane] = s;
+  if (lane == 0) g[L.ob1 + unit] = sb;
+  // dW3[o][i] = sum_r dy[r][o] relu(z2[r][i]);  db3; output o on slice o % 8, waves of unit o / 8
+  for (int o = wave / 2 * MLP_SLICES + slice; o < k; o += MLP_SLICES * MLP_WAVES / 2) {
+    const float dy = DY[o * MLP_LD + mine];
     s = 0.f;
     sb = 0.f;
-    const int i6 = lane < MLP_IN ? lane : 0;
 #pragma unroll
     for (int r = 0; r < MLP_ROWS; ++r) {
-      const float v = lane_of(d1, half * MLP_ROWS + r);
-      s = fmaf(v, XS[(half * MLP_ROWS + r) * MLP_IN + i6], s);
+      const float v = lane_of(dy, r);
+      s = fmaf(v, fmaxf(Z2[lane * MLP_LD + half * MLP_ROWS + r], 0.f), s);
       sb += v;
     }
-    if (lane < MLP_IN) g[L.oW1 + unit * MLP_IN + lane] = s;
-    if (lane == 0) g[L.ob1 + unit] = sb;
-    // dW3[o][i] = sum_r dy[r][o] relu(z2[r][i]);  db3; output o on slice o % 8, wave o / 8
-    for (int o = wave * MLP_SLICES + slice; o < k; o += MLP_SLICES * MLP_WAVES) {
-      const float dy = DY[o * MLP_LD + lane];
-      s = 0.f;
-      sb = 0.f;
-#pragma unroll
-      for (int r = 0; r < MLP_ROWS; ++r) {
-        const float v = lane_of(dy, half * MLP_ROWS + r);
-        s = fmaf(v, fmaxf(Z2[lane * MLP_LD + half * MLP_ROWS + r], 0.f), s);
-        sb += v;
-      }
-      g[L.oW3 + o * MLP_H + lane] = s;
-      if (lane == 0) g[L.ob3 + o] = sb;
-    }
+    g[L.oW3 + o * MLP_H + lane] = s;
+    if (lane == 0) g[L.ob3 + o] = sb;
   }
 }
 
@@ -372,7 +375,7 @@ static MlpPlan mlp_plan(int n, int k, int d) {
 }
 
 static size_t fwdbwd_lds(int k) {
-  return ((size_t)(3 * MLP_H + MLP_WAVES + k) * MLP_LD + 2 * MLP_ROWS * MLP_IN) * 4;
+  return ((size_t)(3 * MLP_H + k) * MLP_LD + 2 * MLP_ROWS * MLP_IN) * 4;
 }
 
 static hipError_t launch_fwdbwd(const float* P, const float* X, const float* Y, int n, int k,
