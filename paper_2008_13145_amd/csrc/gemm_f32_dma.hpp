@@ -125,13 +125,24 @@ __device__ __forceinline__ float f32_at_mnmajor(const float* t, int k, int col) 
 // 128x128 tiles, BK = 32: 4096^3 NT 1051 -> 750 us (131 -> 183 TFLOP/s), NN
 // 1160 -> 803 us; 2048x1024x1536 batch 16 TN 813 -> 610 us.
 //
-// Two kinds of operand do not split: infinities, NaN and values that round
-// to infinity in BF16, whose residual is NaN, and rows or columns whose
-// largest element is so small that the pieces fall below BF16's range.  A
-// wave that meets either (a non-finite sum; a nonzero row with every exponent
-// below 2^-95) computes its block again with FP32 MFMAs straight from memory.
+// Two kinds of operand do not split: infinities and values that round to
+// infinity in BF16, whose residual is NaN, and rows or columns whose largest
+// element is so small that the pieces fall below BF16's range (a NaN does: its
+// row or column of the product is NaN either way).  A wave that meets either
+// (a non-finite sum that no NaN explains; a nonzero row below 2^-95 throughout)
+// computes its block again with FP32 MFMAs straight from memory,
+// the next 8 of K on their way while the present ones multiply; a work-group
+// whose first stage already holds an infinity or a value of 2^48 or more
+// (smaller ones cannot overflow) leaves the split out.  4096^3 NT / TN with such
+// values takes 1.20 / 1.46 ms where the first stage shows them, 1.67 / 1.79 ms where
+// a later one does (FP32 kernels 1.04); two at a time from memory it took 4.6.
+// With NaN 0.69 / 0.65.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+// The larger value, NaN if either is (a single three-operand instruction
+// where two are nested).
+__device__ __forceinline__ float largest(float a, float b) { return __builtin_elementwise_maximum(a, b); }
 
 struct SplitFrag {
   bf16x8 h, m, l;
@@ -144,11 +155,9 @@ struct SplitFrag {
     return __uint_as_float(__builtin_bit_cast(uint32_t, v) & 0xffff0000u);
   }
 
-  // Values 2 p and 2 p + 1; bits collects the OR of their bit patterns (its
-  // exponent field is at least the largest exponent, and below a power of two
-  // exactly when all are).
-  __device__ __forceinline__ void set(int p, const float a, const float b, uint32_t& bits) {
-    bits |= __float_as_uint(a) | __float_as_uint(b);
+  // Values 2 p and 2 p + 1; most collects the largest magnitude, NaN above all.
+  __device__ __forceinline__ void set(int p, const float a, const float b, float& most) {
+    most = largest(most, largest(__builtin_fabsf(a), __builtin_fabsf(b)));
     const bf16x2 hp = __builtin_convertvector(f32x2{a, b}, bf16x2);
     const float ra = a - low(hp), rb = b - high(hp);   // exact
     const bf16x2 mp = __builtin_convertvector(f32x2{ra, rb}, bf16x2);
@@ -160,10 +169,8 @@ struct SplitFrag {
   }
 };
 
-__device__ __forceinline__ bool splits_too_small(uint32_t bits) {
-  return (bits & 0x7fffffffu) != 0u && (bits & 0x7f800000u) < (32u << 23);
-}
-
+// A row or column whose largest magnitude is m has pieces below BF16's range.
+__device__ __forceinline__ bool splits_too_small(float m) { return m > 0.f && m < 0x1p-95f; }
 
 template <int T, int BK>
 struct F32Split {
@@ -186,6 +193,7 @@ gemm_f32_dma_kernel(GemmArgs args) {
   constexpr int NS = Cfg::NS;
   constexpr int WT = Cfg::WT;
   __shared__ __attribute__((aligned(16))) char lds[Cfg::LDS_BYTES];
+  __shared__ int leave;   // split kernels: the first stage holds values that may not split
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -233,11 +241,11 @@ gemm_f32_dma_kernel(GemmArgs args) {
   float acc[SPLIT ? 1 : NACC];
   float total[T == 2 ? 4 : 1] = {};
   f32x16 sacc[SUB][SUB];
-  uint32_t bits_a[SUB], bits_b[SUB];
+  float most_a[SUB], most_b[SUB];   // largest magnitude of each row and column
   if constexpr (SPLIT) {
 #pragma unroll
     for (int i = 0; i < SUB; ++i) {
-      bits_a[i] = bits_b[i] = 0u;
+      most_a[i] = most_b[i] = 0.f;
 #pragma unroll
       for (int j = 0; j < SUB; ++j)
 #pragma unroll
@@ -271,6 +279,7 @@ gemm_f32_dma_kernel(GemmArgs args) {
     }
     if (issued < nk) src.issue(args, m0, n0, lds0 + (issued % NS) * Cfg::STAGE);
   };
+  bool again = false;   // split kernels: FP32 MFMAs from memory
   if constexpr (SPLIT) {
     // 32x32x16 MFMAs: lane half h takes k = h * BK / 2 + 8 s .. + 7 at step s.
     // The fragments of step g + 1 are read and split while the MFMAs of step
@@ -297,8 +306,8 @@ gemm_f32_dma_kernel(GemmArgs args) {
     // pair u (0 .. 8 SUB - 1) of the fetched values: 4 of each fragment
     auto split = [&](Frags& f, int u) {
       const int i = u / 8, p = u % 4;
-      if (u % 8 < 4) f.a[i].set(p, xa[i][p / 2][2 * (p % 2)], xa[i][p / 2][2 * (p % 2) + 1], bits_a[i]);
-      else f.b[i].set(p, xb[i][p / 2][2 * (p % 2)], xb[i][p / 2][2 * (p % 2) + 1], bits_b[i]);
+      if (u % 8 < 4) f.a[i].set(p, xa[i][p / 2][2 * (p % 2)], xa[i][p / 2][2 * (p % 2) + 1], most_a[i]);
+      else f.b[i].set(p, xb[i][p / 2][2 * (p % 2)], xb[i][p / 2][2 * (p % 2) + 1], most_b[i]);
     };
     // MFMA u of a step: six products, the small ones first, of every block
     auto mfma = [&](const Frags& f, int u) {
@@ -331,9 +340,37 @@ gemm_f32_dma_kernel(GemmArgs args) {
 #pragma unroll
       for (int u = 0; u < NM; ++u) mfma(cur, u);
     };
-    if (nk > 0) {
+    if constexpr (Cfg::WAVES >= 4) {
+      if (tid == 0) leave = 0;
       open_stage(0, NS - 1, NS - 2);
-      fetch(0);
+      // only rows and columns of the product count (below, too): beyond them
+      // lies whatever the operands' memory holds
+      bool large = false;
+#pragma nounroll
+      for (int g = S - 1; g >= 0; --g) {
+        fetch(g);
+#pragma unroll
+        for (int i = 0; i < SUB; ++i) {
+          float ma = 0.f, mb = 0.f;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            ma = largest(ma, __builtin_fabsf(xa[i][e / 4][e % 4]));
+            mb = largest(mb, __builtin_fabsf(xb[i][e / 4][e % 4]));
+          }
+          large = large || (32 * i + r32 < M - m0 - wm0 && ma >= 0x1p48f) ||
+                  (32 * i + r32 < N - n0 - wn0 && mb >= 0x1p48f);
+        }
+      }
+      if (__any(large) && lane == 0) leave = 1;
+      vm_wait_barrier<63>();   // the flag; transfers stay in flight
+      again = __builtin_amdgcn_readfirstlane(leave) != 0;
+      if (again) vm_wait_barrier<0>();   // nothing may land in LDS that is no longer ours
+    }
+    if (nk > 0 && !again) {
+      if constexpr (Cfg::WAVES < 4) {
+        open_stage(0, NS - 1, NS - 2);
+        fetch(0);
+      }
 #pragma unroll
       for (int u = 0; u < NP; ++u) split(f0, u);
       int g = 0;
@@ -459,25 +496,31 @@ gemm_f32_dma_kernel(GemmArgs args) {
     const int r32 = lane & 31, h = lane >> 5;
     float nan = 0.f;   // becomes NaN when a sum is not finite
     bool redo = false;
-    // only rows and columns of the product count: beyond them lies whatever
-    // the operands' memory holds
     const int rows = (int)min(M - m0 - wm0, (int64_t)(32 * SUB)), cols = (int)min(N - n0 - wn0, (int64_t)(32 * SUB));
+    // Rows and columns that are stored and hold no NaN (where one does, every
+    // output is NaN in any arithmetic): of rows a mask, of columns the lane's own.
+    uint32_t rows_in[SUB];
+    bool col_in[SUB];
 #pragma unroll
     for (int i = 0; i < SUB; ++i) {
       // both lane halves hold K positions of row / column r32
-      const uint32_t ba = bits_a[i] | (uint32_t)__shfl_xor((int)bits_a[i], 32);
-      const uint32_t bb = bits_b[i] | (uint32_t)__shfl_xor((int)bits_b[i], 32);
-      redo = redo || (32 * i + r32 < rows && splits_too_small(ba)) ||
-             (32 * i + r32 < cols && splits_too_small(bb));
+      const float ma = largest(most_a[i], __shfl_xor(most_a[i], 32));
+      const float mb = largest(most_b[i], __shfl_xor(most_b[i], 32));
+      const bool row_in = 32 * i + r32 < rows && ma == ma;
+      col_in[i] = 32 * i + r32 < cols && mb == mb;
+      redo = redo || (row_in && splits_too_small(ma)) || (col_in[i] && splits_too_small(mb));
+      rows_in[i] = (uint32_t)__ballot(row_in) >> (4 * h);
+    }
+#pragma unroll
+    for (int i = 0; i < SUB; ++i)
 #pragma unroll
       for (int j = 0; j < SUB; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const bool stored = 32 * i + (r >> 2) * 8 + h * 4 + (r & 3) < rows && 32 * j + r32 < cols;
-          nan = fmaf(stored ? sacc[i][j][r] : 0.f, 0.f, nan);
+          const bool in = col_in[j] && (rows_in[i] >> ((r >> 2) * 8 + (r & 3)) & 1u) != 0u;
+          nan = fmaf(in ? sacc[i][j][r] : 0.f, 0.f, nan);
         }
-    }
-    if (__any(redo || nan != nan)) {   // wave-uniform
+    if (again || __any(redo || nan != nan)) {   // wave-uniform
       const float* Af = static_cast<const float*>(args.A) + bz * args.sA;
       const float* Bf = static_cast<const float*>(args.B) + bz * args.sB;
       const float *pa[SUB], *pb[SUB];
@@ -492,8 +535,54 @@ gemm_f32_dma_kernel(GemmArgs args) {
           for (int r = 0; r < 16; ++r) c[i][j][r] = 0.f;
       }
       const int64_t ka = TA == 0 ? 1 : args.lda, kb = TB == 1 ? 1 : args.ldb;
+      int64_t whole = 0;   // K done below, eight at a time
+      // (smaller work-groups' kernels have no registers to spare for it)
+      if constexpr (Cfg::WAVES >= 4) {
+        typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+        struct Eight { float a[SUB][4], b[SUB][4]; };   // half h: k0 + 4 h .. + 3
+        auto get = [&](float (&x)[4], const float* p, int64_t ld, bool kmajor) {
+          if (kmajor) {
+            const f32x4u v = *reinterpret_cast<const f32x4u*>(p);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) x[e] = v[e];
+          } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) x[q] = p[q * ld];
+          }
+        };
+        auto load = [&](Eight& x, int64_t k0) {
+#pragma unroll
+          for (int i = 0; i < SUB; ++i) {
+            get(x.a[i], pa[i] + (k0 + 4 * h) * ka, ka, TA == 0);
+            get(x.b[i], pb[i] + (k0 + 4 * h) * kb, kb, TB == 1);
+          }
+        };
+        auto multiply = [&](const Eight& x) {
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int i = 0; i < SUB; ++i)
+#pragma unroll
+              for (int j = 0; j < SUB; ++j)
+                c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[i][q], x.b[j][q], c[i][j], 0, 0, 0);
+        };
+        whole = K / 8 * 8;
+        Eight x0, x1;
+        load(x0, 0);   // split kernels have K >= 16
 #pragma nounroll
-      for (int64_t k0 = 0; k0 < K; k0 += 2) {
+        for (int64_t k0 = 0; k0 < whole; k0 += 16) {
+          // past the end: the last 8 again, not multiplied
+          load(x1, min(k0 + 8, whole - 8));
+          __builtin_amdgcn_sched_barrier(0);
+          multiply(x0);
+          if (k0 + 8 >= whole) break;
+          load(x0, min(k0 + 16, whole - 8));
+          __builtin_amdgcn_sched_barrier(0);
+          multiply(x1);
+        }
+      }
+#pragma nounroll
+      for (int64_t k0 = whole; k0 < K; k0 += 2) {
         const int64_t k = k0 + h;
         float a[SUB], b[SUB];
 #pragma unroll
