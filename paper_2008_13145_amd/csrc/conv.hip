@@ -22,6 +22,7 @@
 #include <stdint.h>
 
 #include "kt_internal.hpp"
+#include "wino_patch.hpp"
 
 namespace kt {
 
@@ -117,21 +118,9 @@ wino_input_kernel(const V* __restrict__ x, Dims<I> d, I tH, I tW, V* __restrict_
     const I by = t / tW, tx = t - by * tW;
     const I b = by / tH, ty = by - b * tH;
     const I y0 = 2 * ty - d.pad, x0 = 2 * tx - d.pad;
-    // every load from inside the image, what lies in the padding cleared after
-    // it: no branch between the 16 loads
     V v[4][4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const I yi = min(max(y0 + u, (I)0), d.H - 1), xj = min(max(x0 + w, (I)0), d.W - 1);
-        v[u][w] = x[((b * d.H + yi) * d.W + xj) * d.C + c];
-      }
-#pragma unroll
-    for (int u = 0; u < 4; ++u)
-#pragma unroll
-      for (int w = 0; w < 4; ++w)
-        if (y0 + u < 0 || y0 + u >= d.H || x0 + w < 0 || x0 + w >= d.W) v[u][w] = zero_of<V>();
+    wino_patch(d.H, d.W, y0, x0, zero_of<V>(),
+               [&](I yi, I xj) { return x[((b * d.H + yi) * d.W + xj) * d.C + c]; }, v);
     V r[4][4];   // Bt d
 #pragma unroll
     for (int w = 0; w < 4; ++w) {
