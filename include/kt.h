@@ -153,7 +153,12 @@ kt_status kt_kernel_workspace_bytes(kt_handle h, kt_dtype dtype, const kt_shape*
  * untouched by the caller while kt_gemm work queued on any stream may use
  * it, and kt_gemm calls of one handle that run split-K kernels on different
  * streams at once race on it.  Without it (or when it is too small for a
- * product) split-K kernels run as their base configuration unsplit. */
+ * product) split-K kernels run as their base configuration unsplit.
+ * The slices of deep FP32 products that the selector gives a plain kernel
+ * (kt_gemm, kt_conv2d) take their planes from its end.  Those calls may be on
+ * any streams: the handle orders them after one another, keeps them clear of
+ * the part that split-K kernels have used and runs them unsplit under stream
+ * capture.  That order is the handle's: give two handles two workspaces. */
 kt_status kt_set_workspace(kt_handle h, void* workspace, size_t bytes);
 
 /* ------------------------------------------------------------------- GEMM */
@@ -167,8 +172,11 @@ kt_status kt_set_workspace(kt_handle h, void* workspace, size_t bytes);
  * see kt_num_kernels; a variant takes its partial planes from the workspace
  * set with kt_set_workspace); -1 asks the fitted selector, whose pick may be
  * a split-K variant.  With -1, an FP32 product of batch 1 with K >= 1536 and at
- * most 128 tiles of the picked configuration runs in 4 or 8 slices of K when
- * that workspace holds their partial planes.
+ * most 128 tiles of the picked configuration runs in 8 slices of K (4 from 65
+ * tiles on) when the end of that workspace holds their partial planes and the
+ * stream is not being captured; its bits are then those of kt_gemm_splitk with
+ * that configuration and slice count, not of kt_gemm with the id kt_select
+ * returns.
  * With beta == 0, C is never read (NaN in C does not propagate).  M, N or
  * batch == 0 is a no-op; K == 0 gives C = beta * C.  Unaligned pointers or
  * leading dimensions are never an error (FP32 rows load as dword-aligned
@@ -303,9 +311,10 @@ kt_status kt_conv2d_workspace_bytes(const kt_conv_shape* c, kt_conv_algo algo, i
  * bias; Cout floats), y and workspace are device pointers; y must not alias
  * x or the workspace.  config_id: FP32 configuration of the GEMM, -1 = the
  * kernel the fitted selector picks for kt_conv2d_gemm_shape (with splits = 1
- * and im2col, a selected split-K kernel runs split with the partial planes in
- * the kt_set_workspace buffer when they fit; otherwise its configuration
- * runs with the layer's `splits`).  splits (im2col only; Winograd
+ * and im2col, a selected split-K kernel, or a plain one on a deep product as
+ * kt_gemm has it, runs split with the partial planes in the kt_set_workspace
+ * buffer when they fit and that buffer is not the layer's workspace; otherwise
+ * its configuration runs with the layer's `splits`).  splits (im2col only; Winograd
  * takes 0 or 1 and never splits): 1 = the plain GEMM, otherwise the GEMM
  * runs as kt_gemm_splitk with this splits value (0 = automatic), which suits
  * the fully connected layers of a single image (M = 1, deep K).  Empty n, Ho

@@ -194,6 +194,7 @@ kt_status kt_destroy(kt_handle hh) {
     (void)hipSetDevice(h->device);
     for (int d = 0; d < NUM_DTYPES; ++d) free_selector_device(h, d);
     if (h->scratch) (void)hipFree(h->scratch);
+    if (h->deep_done) (void)hipEventDestroy(h->deep_done);
     if (h->d_lut) (void)hipFree(h->d_lut);
   }
   delete h;
@@ -257,8 +258,21 @@ kt_status kt_set_workspace(kt_handle hh, void* workspace, size_t bytes) {
   Ctx* h = reinterpret_cast<Ctx*>(hh);
   if (!h) return fail(nullptr, KT_EINVAL, "NULL handle");
   if (!workspace && bytes) return fail(h, KT_EINVAL, "NULL workspace with a nonzero size");
+  if (h->device >= 0 && workspace && !h->deep_done) {
+    hipError_t e = hipEventCreateWithFlags(&h->deep_done, hipEventDisableTiming | hipEventDisableSystemFence);
+    if (e != hipSuccess) { h->deep_done = nullptr; return hip_fail(h, e, "workspace event"); }
+  }
   h->gemm_ws = workspace;
   h->gemm_ws_bytes = workspace ? bytes : 0;
+  if (!workspace) return KT_OK;
+  // where split-K kernels have been in the last buffer stays theirs in one
+  // that overlaps it; deep products may have been anywhere in the new one
+  const uintptr_t begin = (uintptr_t)workspace, end = begin + bytes, low_end = h->ws_begin + h->ws_low;
+  const bool overlap = begin < h->ws_end && h->ws_begin < end;
+  h->ws_low = overlap && low_end > begin ? low_end - begin : 0;
+  h->ws_high = h->deep_used ? bytes : 0;
+  h->ws_begin = begin;
+  h->ws_end = end;
   return KT_OK;
 }
 
@@ -296,13 +310,13 @@ kt_status kt_gemm(kt_handle hh, kt_dtype in_dtype, const kt_shape* s, float alph
   }
   if (!valid_kernel(h, in_dtype, id)) return fail(h, KT_EINVAL, "kernel id out of range");
   if (config_id < 0) {
-    const int32_t slices = deep_slices(h, in_dtype, s, id);
-    const size_t planes = split_plane_bytes(s, slices);
-    if (planes > 0 && h->gemm_ws && h->gemm_ws_bytes >= planes)
-      return splitk_gemm(h, in_dtype, s, slices, alpha, A, lda, strideA, B, ldb, strideB, beta, C, ldc,
-                         strideC, scaleA, scaleB, id, h->gemm_ws, h->gemm_ws_bytes, stream, nullptr,
-                         nullptr, 0, nullptr);
+    bool ran = false;
+    st = run_deep(h, in_dtype, s, alpha, A, lda, strideA, B, ldb, strideB, beta, C, ldc, strideC, id,
+                  nullptr, 0, nullptr, 0, stream, &ran, nullptr);
+    if (st != KT_OK || ran) return st;
   }
+  st = order_split(h, kernel_plane_bytes(h, in_dtype, s, id), (hipStream_t)stream);
+  if (st != KT_OK) return st;
   return run_kernel(h, in_dtype, s, alpha, A, lda, strideA, B, ldb, strideB, beta, C, ldc,
                     strideC, scaleA, scaleB, id, h->gemm_ws, h->gemm_ws_bytes, (hipStream_t)stream);
 }

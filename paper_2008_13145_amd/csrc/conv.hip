@@ -388,20 +388,22 @@ kt_status kt_conv2d(kt_handle hh, kt_conv_algo algo, const kt_conv_shape* c, con
         if ((st = select_config(h, KT_F32, &gs, &sel)) != KT_OK) return st;
         cfg = kernel_base(h, KT_F32, sel);
       }
-      int32_t slices = 1;
-      if (sel >= 0) {
-        slices = kernel_slices(h, KT_F32, sel);
-        if (slices == 1) slices = deep_slices(h, KT_F32, &gs, sel);
-      }
-      const size_t planes = split_plane_bytes(&gs, slices);
-      if (planes > 0 && h->gemm_ws && h->gemm_ws_bytes >= planes) {
-        // a selected split-K kernel runs split, its planes in the handle's
-        // workspace, and its reduction applies the bias and the activation
-        st = splitk_gemm(h, KT_F32, &gs, slices, 1.f, col, gs.K,
+      const size_t planes = sel >= 0 ? kernel_plane_bytes(h, KT_F32, &gs, sel) : 0;
+      bool ran = false;
+      // a selected split-K kernel, or a plain one on a deep product, runs
+      // split, its planes in the handle's workspace, and its reduction applies
+      // the bias and the activation
+      if (sel >= 0)
+        st = run_deep(h, KT_F32, &gs, 1.f, col, gs.K, gs.M * gs.K, w, d.O, gs.K * d.O, 0.f, y, d.O,
+                      gs.M * d.O, sel, ws, need, bias, relu, stream, &ran, &fused);
+      if (st == KT_OK && !ran) st = order_split(h, planes, s);
+      if (st != KT_OK) return st;
+      if (!ran && planes > 0 && h->gemm_ws && h->gemm_ws_bytes >= planes) {
+        st = splitk_gemm(h, KT_F32, &gs, kernel_slices(h, KT_F32, sel), 1.f, col, gs.K,
                          gs.M * gs.K, w, d.O, gs.K * d.O, 0.f, y, d.O, gs.M * d.O, nullptr,
                          nullptr, cfg, h->gemm_ws, h->gemm_ws_bytes, stream, nullptr, bias, relu,
                          &fused);
-      } else {
+      } else if (!ran) {
         st = launch_gemm(h, KT_F32, &gs, 1.f, col, gs.K, gs.M * gs.K, w, d.O, gs.K * d.O, 0.f, y,
                          d.O, gs.M * d.O, nullptr, nullptr, cfg, s);
       }

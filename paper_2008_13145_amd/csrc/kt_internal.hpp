@@ -69,8 +69,15 @@ struct Ctx {
   void* d_lut = nullptr;           // device sigmoid table (handle-owned)
   kt_grouped_opts grouped_best{};  // autotuner result for grouped GEMM
   bool grouped_tuned = false;
-  void* gemm_ws = nullptr;         // caller's workspace for split-K kernels run by kt_gemm
+  void* gemm_ws = nullptr;         // caller's workspace for partial planes of kt_gemm and kt_conv2d
   size_t gemm_ws_bytes = 0;
+  // Split-K kernels take its start, deep products of plain picks its end
+  // (splitk.hip: run_deep).
+  uintptr_t ws_begin = 0, ws_end = 0;   // the last workspace set
+  size_t ws_low = 0;               // most bytes split-K kernels have taken from its start
+  size_t ws_high = 0;              // most bytes deep products have taken from its end
+  hipEvent_t deep_done = nullptr;  // the last deep product in slices
+  bool deep_used = false;          // deep_done has been recorded
   void* noalloc_scratch = nullptr; // device address of the static split-K scratch
   bool forbid_alloc = false;       // set while an entry point that must not allocate runs
   bool full_rows = false;          // caller: every operand row is allocated to its full ld
@@ -122,6 +129,17 @@ constexpr size_t SPLIT_PLANE_CAP = (size_t)256 << 20;
 size_t kernel_plane_bytes(const Ctx* h, int dtype, const kt_shape* s, int32_t id);
 // Slices of K for a plain kernel that the selector picked (1: unsplit).
 int32_t deep_slices(const Ctx* h, int dtype, const kt_shape* s, int32_t id);
+// Run such a product in its slices, with their partial planes at the end of
+// the handle's workspace; *ran = false, and nothing launched, where it has to
+// run unsplit instead.  `busy` is memory the call itself works in, which the
+// planes must not touch.  Bias, ReLU and *epilogue_done as splitk_gemm.
+kt_status run_deep(Ctx* h, kt_dtype dtype, const kt_shape* s, float alpha, const void* A,
+                   int64_t lda, int64_t sA, const void* B, int64_t ldb, int64_t sB, float beta,
+                   float* C, int64_t ldc, int64_t sC, int32_t id, const void* busy,
+                   size_t busy_bytes, const float* bias, int32_t relu, void* stream, bool* ran,
+                   bool* epilogue_done);
+// Before a split-K kernel takes `bytes` from the start of the workspace on a stream.
+kt_status order_split(Ctx* h, size_t bytes, hipStream_t stream);
 // The same for a slice count (no handle needed).
 size_t split_plane_bytes(const kt_shape* s, int32_t slices);
 

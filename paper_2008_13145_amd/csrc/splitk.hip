@@ -152,6 +152,67 @@ size_t kernel_plane_bytes(const Ctx* h, int dtype, const kt_shape* s, int32_t id
   return split_plane_bytes(s, kernel_slices(h, dtype, id));
 }
 
+// The caller of a plain kernel need not know that it works in the workspace,
+// so nothing may depend on the caller keeping its streams apart:
+// - the planes lie at the end of the workspace, clear of what split-K kernels
+//   have taken from its start (those calls leave no event; where the two would
+//   overlap the product runs unsplit);
+// - a deep product waits for the one before it, whatever stream that is on, and
+//   so does a split-K kernel that reaches into their part;
+// - under stream capture it runs unsplit: nothing orders a graph's replays
+//   against the handle's later calls.
+// The event costs 2 us on the stream (an event that also fenced for the host 3.5),
+// the wait for it nothing on the same stream.
+kt_status run_deep(Ctx* h, kt_dtype dtype, const kt_shape* s, float alpha, const void* A,
+                   int64_t lda, int64_t sA, const void* B, int64_t ldb, int64_t sB, float beta,
+                   float* C, int64_t ldc, int64_t sC, int32_t id, const void* busy,
+                   size_t busy_bytes, const float* bias, int32_t relu, void* stream, bool* ran,
+                   bool* epilogue_done) {
+  *ran = false;
+  const int32_t slices = deep_slices(h, dtype, s, id);
+  const size_t planes = split_plane_bytes(s, slices);
+  if (planes == 0 || !h->gemm_ws || h->gemm_ws_bytes < planes || !h->deep_done) return KT_OK;
+  const size_t off = (h->gemm_ws_bytes - planes) & ~(size_t)255;
+  char* at = (char*)h->gemm_ws + off;
+  if (off < h->ws_low) return KT_OK;
+  if (busy_bytes > 0 && (uintptr_t)busy < (uintptr_t)at + planes &&
+      (uintptr_t)at < (uintptr_t)busy + busy_bytes)
+    return KT_OK;
+  hipStreamCaptureStatus capture;
+  if (hipStreamIsCapturing((hipStream_t)stream, &capture) != hipSuccess) {
+    (void)hipGetLastError();   // the null stream while another one captures
+    return KT_OK;
+  }
+  if (capture != hipStreamCaptureStatusNone) return KT_OK;
+  hipError_t e;
+  if (h->deep_used && (e = hipStreamWaitEvent((hipStream_t)stream, h->deep_done, 0)) != hipSuccess)
+    return hip_fail(h, e, "wait for the workspace");
+  *ran = true;
+  const kt_status st = splitk_gemm(h, dtype, s, slices, alpha, A, lda, sA, B, ldb, sB, beta, C, ldc,
+                                   sC, nullptr, nullptr, id, at, planes, stream, nullptr, bias, relu,
+                                   epilogue_done);
+  // also after a failure: some of the slices may be on their way
+  if ((e = hipEventRecord(h->deep_done, (hipStream_t)stream)) != hipSuccess)
+    return hip_fail(h, e, "workspace event");
+  h->deep_used = true;
+  if (h->gemm_ws_bytes - off > h->ws_high) h->ws_high = h->gemm_ws_bytes - off;
+  return st;
+}
+
+kt_status order_split(Ctx* h, size_t bytes, hipStream_t stream) {
+  if (bytes == 0 || !h->gemm_ws || h->gemm_ws_bytes < bytes) return KT_OK;   // runs unsplit
+  if (bytes > h->ws_low) h->ws_low = bytes;
+  if (!h->deep_used || bytes + h->ws_high <= h->gemm_ws_bytes) return KT_OK;
+  hipStreamCaptureStatus capture;
+  if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
+    (void)hipGetLastError();
+    return KT_OK;
+  }
+  if (capture != hipStreamCaptureStatusNone) return KT_OK;   // the caller orders a graph's replays
+  const hipError_t e = hipStreamWaitEvent(stream, h->deep_done, 0);
+  return e == hipSuccess ? KT_OK : hip_fail(h, e, "wait for the workspace");
+}
+
 kt_status run_kernel(Ctx* h, int dtype, const kt_shape* s, float alpha, const void* A,
                      int64_t lda, int64_t sA, const void* B, int64_t ldb, int64_t sB, float beta,
                      float* C, int64_t ldc, int64_t sC, const float* scaleA, const float* scaleB,
