@@ -614,7 +614,9 @@ kt_status kt_fit_selector_validated(kt_handle h, kt_dtype dtype, const kt_shape*
  * whose M, N, K or batch lies outside the range the selector was fitted on
  * is not given to the model; the chosen configurations are timed on it once
  * (scratch as above, synchronizing) and the fastest is cached for the
- * shape.  Entry points that must not allocate keep the model's pick. */
+ * shape.  Kernels are timed as kt_gemm(-1) runs them with the workspace set at
+ * that time: deep products of plain kernels in slices, see kt_gemm.  Entry
+ * points that must not allocate keep the model's pick. */
 kt_status kt_select(kt_handle h, kt_dtype dtype, const kt_shape* s, int32_t* config_id);
 
 /* The out-of-range fallback of kt_select for the selector of a dtype (kept

@@ -195,9 +195,11 @@ static int64_t elem_bytes_sel(int dtype) { return dtype == KT_F32 ? 4 : dtype ==
 
 // Time the candidate kernels (those whose configuration is compiled for the
 // shape's layout) on handle-owned scratch operands (generated in FP32 and
-// converted for BF16 / FP8), split-K variants with scratch partial planes:
-// one untimed launch, then three timed ones each; the fastest (first on
-// ties) wins.  Allocates the scratch on first use and synchronizes.
+// converted for BF16 / FP8), split-K variants with scratch partial planes and
+// plain kernels in the slices that kt_gemm(-1) would run them in with the
+// workspace at hand (run_deep, its event included): one untimed launch, then
+// three timed ones each; the fastest (first on ties) wins.  Allocates the
+// scratch on first use and synchronizes.
 static kt_status time_candidates(Ctx* h, int dtype, const kt_shape* s,
                                  const std::vector<int32_t>& cands, int32_t* out) {
   if (!need_device(h)) return KT_EINVAL;
@@ -222,7 +224,12 @@ static kt_status time_candidates(Ctx* h, int dtype, const kt_shape* s,
   const int64_t offT = offS + 256;   // FP32 staging for BF16 / FP8 operands
   const int64_t offW = offT + r256(dtype == KT_F32 ? 0 : std::max(nA, nB) * 4);   // split-K planes
   size_t planes = 0;
-  for (int32_t id : cands) planes = std::max(planes, kernel_plane_bytes(h, dtype, s, id));
+  auto deep_planes = [&](int32_t id) {
+    const size_t b = split_plane_bytes(s, deep_slices(h, dtype, s, id));
+    return h->gemm_ws && b <= h->gemm_ws_bytes ? b : 0;
+  };
+  for (int32_t id : cands)
+    planes = std::max(planes, std::max(kernel_plane_bytes(h, dtype, s, id), deep_planes(id)));
   const size_t need = (size_t)offW + planes + 256;
   if (h->scratch_bytes < need) {
     if (h->scratch) (void)hipFree(h->scratch);
@@ -256,9 +263,14 @@ static kt_status time_candidates(Ctx* h, int dtype, const kt_shape* s,
       if (st != KT_OK) return st;
     }
   }
-  hipEvent_t e0, e1;
+  hipEvent_t e0, e1, after;
   if ((e = hipEventCreate(&e0)) != hipSuccess) return hip_fail(h, e, "event");
   if ((e = hipEventCreate(&e1)) != hipSuccess) { (void)hipEventDestroy(e0); return hip_fail(h, e, "event"); }
+  if ((e = hipEventCreateWithFlags(&after, hipEventDisableTiming | hipEventDisableSystemFence)) != hipSuccess) {
+    (void)hipEventDestroy(e0);
+    (void)hipEventDestroy(e1);
+    return hip_fail(h, e, "event");
+  }
   // Two rounds: all candidates, then again those within 1.5x of the fastest,
   // each taken at its better time.  In one round the candidate that happens
   // to run while the clock still settles loses by up to 15 % and is cached
@@ -273,7 +285,16 @@ static kt_status time_candidates(Ctx* h, int dtype, const kt_shape* s,
       const int32_t id = cands[ci];
       if (!find_launcher(h, dtype, kernel_base(h, dtype, id), s->transA, s->transB)) continue;
       if (round == 1 && t[ci] > limit) continue;
+      const bool deep = deep_planes(id) > 0;
       auto launch = [&]() {
+        if (deep) {
+          const kt_status r = splitk_gemm(h, (kt_dtype)dtype, s, deep_slices(h, dtype, s, id), 1.f, A,
+                                          lda, a_rows * lda, B, ldb, b_rows * ldb, 0.f, C, ldc,
+                                          s->M * ldc, scales, scales + 1, id, base + offW, planes,
+                                          nullptr, nullptr, nullptr, 0, nullptr);
+          if (r == KT_OK) (void)hipEventRecord(after, nullptr);
+          return r;
+        }
         return run_kernel(h, dtype, s, 1.f, A, lda, a_rows * lda, B, ldb, b_rows * ldb, 0.f, C, ldc,
                           s->M * ldc, scales, scales + 1, id, base + offW, planes, nullptr);
       };
@@ -293,6 +314,7 @@ static kt_status time_candidates(Ctx* h, int dtype, const kt_shape* s,
     if (t[ci] >= 0.f && t[ci] == best_ms && best < 0) best = cands[ci];
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
+  (void)hipEventDestroy(after);
   if (st != KT_OK) return st;
   if (best < 0) return fail(h, KT_EUNSUPPORTED, "no candidate configuration compiled for this layout");
   *out = best;

@@ -135,8 +135,9 @@ size_t split_plane_bytes(const kt_shape* s, int32_t slices) {
 // kernels, and a pruned set need not hold a split-K variant; one tile per
 // work-group then walks all of K alone: with (32, 32, 2, 64), 20 us at K = 2048
 // and 38 us at K = 4000 whatever M and N, against 12 and 18 us in 8 slices.
-// The line lies where two launches and the partial sums cost what the shorter
-// walk saves: K = 1024 loses 5 to 15 %, K = 1500 gains 5 to 15 %; up to 128 tiles
+// The line lies where the launches, the partial sums and the event (run_deep)
+// cost what the shorter walk saves: K = 1024 loses, K = 1536 gains 5 to 10 %
+// (17.0 -> 13.1 us and 2 for the event at 33 x 70 and 256 x 256); up to 128 tiles
 // slices gain (1 x 4096 x 25088: 219 -> 80 us in 4), at 160 in 4 still 10 to 25 %
 // at K >= 2048 but lose at 1500, at 252 they gain nothing.
 int32_t deep_slices(const Ctx* h, int dtype, const kt_shape* s, int32_t id) {
