@@ -147,6 +147,12 @@ kt_status kt_get_kernel(kt_handle h, kt_dtype dtype, int32_t id, kt_config* cfg,
  * Host only. */
 kt_status kt_kernel_workspace_bytes(kt_handle h, kt_dtype dtype, const kt_shape* s, int32_t id,
                                     size_t* bytes);
+/* Partial-plane bytes that kt_gemm(config_id = -1) takes from the workspace of
+ * kt_set_workspace on shape s: those of the kernel kt_select returns, or of the
+ * slices it runs a plain one in on a deep FP32 product (0 when it runs
+ * unsplit).  The shape is selected as kt_select does.  The same for the
+ * product of an im2col layer (kt_conv2d_gemm_shape). */
+kt_status kt_gemm_workspace_bytes(kt_handle h, kt_dtype dtype, const kt_shape* s, size_t* bytes);
 /* Device workspace (caller-owned, may be NULL with bytes 0) that kt_gemm
  * gives a split-K kernel for its partial planes, whether selected or forced.
  * The handle keeps the pointer, not the memory: it must stay allocated and

@@ -115,6 +115,7 @@ _SIGS = {
     "kt_kernel_workspace_bytes": (c_i32, [c_vp, c_i32, ctypes.POINTER(Shape), c_i32,
                                           ctypes.POINTER(c_sz)]),
     "kt_set_workspace": (c_i32, [c_vp, c_vp, c_sz]),
+    "kt_gemm_workspace_bytes": (c_i32, [c_vp, c_i32, ctypes.POINTER(Shape), ctypes.POINTER(c_sz)]),
     "kt_dma_pipeline": (c_i32, [c_vp, c_i32, ctypes.POINTER(Shape), c_vp, c_i64, c_i64, c_vp, c_i64,
                                c_i64, ctypes.POINTER(c_i32)]),
     "kt_set_full_rows": (c_i32, [c_vp, c_i32]),
@@ -301,6 +302,14 @@ class Handle:
                                                      int(id), ctypes.byref(b)))
         return b.value
 
+    def gemm_workspace_bytes(self, M, N, K, batch=1, transA=0, transB=0, dtype=F32) -> int:
+        """Partial planes that gemm(config_id=-1) takes from the workspace."""
+        b = c_sz()
+        self._check(self.L.kt_gemm_workspace_bytes(self.h, dtype,
+                                                   ctypes.byref(shape(M, N, K, batch, transA, transB)),
+                                                   ctypes.byref(b)))
+        return b.value
+
     def dma_pipeline(self, dtype, shp: Shape, A, lda, sA, B, ldb, sB) -> bool:
         """True when BF16 / FP8 kernels run these operands through the LDS DMA pipeline."""
         v = c_i32()
@@ -313,7 +322,8 @@ class Handle:
         self._check(self.L.kt_set_full_rows(self.h, 1 if enabled else 0))
 
     def set_workspace(self, ws, ws_bytes=None):
-        """Device buffer (tensor or pointer) kt_gemm gives split-K kernels; None clears it."""
+        """Device buffer (tensor or pointer) for the partial planes of gemm and
+        conv2d (split-K kernels, deep products of plain picks); None clears it."""
         if ws is None:
             self._check(self.L.kt_set_workspace(self.h, None, 0))
             return

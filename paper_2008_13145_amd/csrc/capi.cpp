@@ -288,6 +288,24 @@ kt_status kt_kernel_workspace_bytes(kt_handle hh, kt_dtype dtype, const kt_shape
   return KT_OK;
 }
 
+kt_status kt_gemm_workspace_bytes(kt_handle hh, kt_dtype dtype, const kt_shape* s, size_t* bytes) {
+  Ctx* h = reinterpret_cast<Ctx*>(hh);
+  if (!h || !s || !bytes) return fail(h, KT_EINVAL, "NULL argument");
+  if ((int)dtype < 0 || (int)dtype >= NUM_DTYPES) return fail(h, KT_EINVAL, "bad dtype");
+  if (s->M < 0 || s->N < 0 || s->K < 0 || s->batch < 0)
+    return fail(h, KT_EINVAL, "negative M, N, K or batch");
+  if (s->M == 0 || s->N == 0 || s->batch == 0) {
+    *bytes = 0;
+    return KT_OK;
+  }
+  int32_t id = -1;
+  const kt_status st = select_config(h, dtype, s, &id);
+  if (st != KT_OK) return st;
+  const size_t deep = split_plane_bytes(s, deep_slices(h, dtype, s, id));
+  *bytes = deep > 0 ? deep : kernel_plane_bytes(h, dtype, s, id);
+  return KT_OK;
+}
+
 kt_status kt_gemm(kt_handle hh, kt_dtype in_dtype, const kt_shape* s, float alpha, const void* A,
                   int64_t lda, int64_t strideA, const void* B, int64_t ldb, int64_t strideB,
                   float beta, float* C, int64_t ldc, int64_t strideC, const float* scaleA,
