@@ -102,9 +102,10 @@ __device__ __forceinline__ float f32_at_mnmajor(const float* t, int k, int col) 
 }
 
 // FP32 products on the BF16 matrix cores (T = 8 with BK >= 16).  A float
-// is exactly the sum of three BF16 values, x = h + m + l (each the rounding of
-// what is left: 24 bits as 8 + 8 + 8), and
-//   a b = ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + terms < 2^-25 |a b|,
+// of 2^-110 or more is exactly the sum of three BF16 values, x = h + m + l (each
+// the rounding of what is left: 24 bits as 8 + 8 + 8; below, the last piece ends
+// at BF16's smallest subnormal and 2^-134 may be left), and
+//   a b = ah bh + (ah bm + am bh) + (ah bl + am bm + al bh) + terms < 2^-24 |a b| in all,
 // so six BF16 MFMAs, whose products are exact and whose sums are FP32, take
 // the place of the eight times slower FP32 ones.  Each 16-deep step adds the
 // small products first.  The result is nearer to the exact product than the
@@ -126,10 +127,11 @@ __device__ __forceinline__ float f32_at_mnmajor(const float* t, int k, int col) 
 // 1160 -> 803 us; 2048x1024x1536 batch 16 TN 813 -> 610 us.
 //
 // Two kinds of operand do not split: infinities and values that round to
-// infinity in BF16, whose residual is NaN, and rows or columns whose largest
-// element is so small that the pieces fall below BF16's range (a NaN does: its
-// row or column of the product is NaN either way).  A wave that meets either
-// (a non-finite sum that no NaN explains; a nonzero row below 2^-95 throughout)
+// infinity in BF16, whose residual is NaN, and values below 2^-110 (a NaN does:
+// its row or column of the product is NaN either way).  A wave that meets
+// either where it shows (a non-finite sum that no NaN explains; a sum below
+// 2^27 times what its operands' pieces may leave out of it, where any left
+// something out: one OR per two values, 2.5 % of the kernel)
 // computes its block again with FP32 MFMAs straight from memory,
 // the next 8 of K on their way while the present ones multiply; a work-group
 // whose first stage already holds an infinity or a value of 2^48 or more
@@ -155,22 +157,23 @@ struct SplitFrag {
     return __uint_as_float(__builtin_bit_cast(uint32_t, v) & 0xffff0000u);
   }
 
-  // Values 2 p and 2 p + 1; most collects the largest magnitude, NaN above all.
-  __device__ __forceinline__ void set(int p, const float a, const float b, float& most) {
+  // Values 2 p and 2 p + 1; most collects the largest magnitude, NaN above all,
+  // left the bits of what the first two pieces leave: the third takes it
+  // whole unless one of the lower 16 is set.
+  __device__ __forceinline__ void set(int p, const float a, const float b, float& most, uint32_t& left) {
     most = largest(most, largest(__builtin_fabsf(a), __builtin_fabsf(b)));
     const bf16x2 hp = __builtin_convertvector(f32x2{a, b}, bf16x2);
     const float ra = a - low(hp), rb = b - high(hp);   // exact
     const bf16x2 mp = __builtin_convertvector(f32x2{ra, rb}, bf16x2);
     const float qa = ra - low(mp), qb = rb - high(mp);
+    // (asm: reassociated by the compiler, the chain of ORs keeps its inputs in registers)
+    asm("v_or3_b32 %0, %0, %1, %2" : "+v"(left) : "v"(qa), "v"(qb));
     const bf16x2 lp = __builtin_convertvector(f32x2{qa, qb}, bf16x2);
     h[2 * p] = hp[0]; h[2 * p + 1] = hp[1];
     m[2 * p] = mp[0]; m[2 * p + 1] = mp[1];
     l[2 * p] = lp[0]; l[2 * p + 1] = lp[1];
   }
 };
-
-// A row or column whose largest magnitude is m has pieces below BF16's range.
-__device__ __forceinline__ bool splits_too_small(float m) { return m > 0.f && m < 0x1p-95f; }
 
 template <int T, int BK>
 struct F32Split {
@@ -242,6 +245,7 @@ gemm_f32_dma_kernel(GemmArgs args) {
   float total[T == 2 ? 4 : 1] = {};
   f32x16 sacc[SUB][SUB];
   float most_a[SUB], most_b[SUB];   // largest magnitude of each row and column
+  uint32_t left = 0u;               // a lower half that is not zero: a value that does not split
   if constexpr (SPLIT) {
 #pragma unroll
     for (int i = 0; i < SUB; ++i) {
@@ -306,8 +310,8 @@ gemm_f32_dma_kernel(GemmArgs args) {
     // pair u (0 .. 8 SUB - 1) of the fetched values: 4 of each fragment
     auto split = [&](Frags& f, int u) {
       const int i = u / 8, p = u % 4;
-      if (u % 8 < 4) f.a[i].set(p, xa[i][p / 2][2 * (p % 2)], xa[i][p / 2][2 * (p % 2) + 1], most_a[i]);
-      else f.b[i].set(p, xb[i][p / 2][2 * (p % 2)], xb[i][p / 2][2 * (p % 2) + 1], most_b[i]);
+      if (u % 8 < 4) f.a[i].set(p, xa[i][p / 2][2 * (p % 2)], xa[i][p / 2][2 * (p % 2) + 1], most_a[i], left);
+      else f.b[i].set(p, xb[i][p / 2][2 * (p % 2)], xb[i][p / 2][2 * (p % 2) + 1], most_b[i], left);
     };
     // MFMA u of a step: six products, the small ones first, of every block
     auto mfma = [&](const Frags& f, int u) {
@@ -501,15 +505,14 @@ gemm_f32_dma_kernel(GemmArgs args) {
     // output is NaN in any arithmetic): of rows a mask, of columns the lane's own.
     uint32_t rows_in[SUB];
     bool col_in[SUB];
+    float row_most[SUB], col_most[SUB];
 #pragma unroll
     for (int i = 0; i < SUB; ++i) {
       // both lane halves hold K positions of row / column r32
-      const float ma = largest(most_a[i], __shfl_xor(most_a[i], 32));
-      const float mb = largest(most_b[i], __shfl_xor(most_b[i], 32));
-      const bool row_in = 32 * i + r32 < rows && ma == ma;
-      col_in[i] = 32 * i + r32 < cols && mb == mb;
-      redo = redo || (row_in && splits_too_small(ma)) || (col_in[i] && splits_too_small(mb));
-      rows_in[i] = (uint32_t)__ballot(row_in) >> (4 * h);
+      row_most[i] = largest(most_a[i], __shfl_xor(most_a[i], 32));
+      col_most[i] = largest(most_b[i], __shfl_xor(most_b[i], 32));
+      col_in[i] = 32 * i + r32 < cols && col_most[i] == col_most[i];
+      rows_in[i] = (uint32_t)__ballot(32 * i + r32 < rows && row_most[i] == row_most[i]) >> (4 * h);
     }
 #pragma unroll
     for (int i = 0; i < SUB; ++i)
@@ -520,6 +523,21 @@ gemm_f32_dma_kernel(GemmArgs args) {
           const bool in = col_in[j] && (rows_in[i] >> ((r >> 2) * 8 + (r & 3)) & 1u) != 0u;
           nan = fmaf(in ? sacc[i][j][r] : 0.f, 0.f, nan);
         }
+    if (__any((left & 0xffffu) != 0u)) {
+      // what the pieces leave out of a sum is at most 2^-134 K (row_most + col_most)
+      const float unit = (float)K * 0x1p-107f;
+#pragma unroll
+      for (int i = 0; i < SUB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = (r >> 2) * 8 + (r & 3);
+          const float m = __shfl(row_most[i], row + 4 * h);
+#pragma unroll
+          for (int j = 0; j < SUB; ++j)
+            redo = redo || (col_in[j] && (rows_in[i] >> row & 1u) != 0u && m > 0.f && col_most[j] > 0.f &&
+                            !(__builtin_fabsf(sacc[i][j][r]) >= unit * (m + col_most[j])));
+        }
+    }
     if (again || __any(redo || nan != nan)) {   // wave-uniform
       const float* Af = static_cast<const float*>(args.A) + bz * args.sA;
       const float* Bf = static_cast<const float*>(args.B) + bz * args.sB;
