@@ -68,6 +68,7 @@ template <int BM, int BN, int T, int BK, int TA, int TB>
 __device__ __forceinline__ void f32_dma_zero_tail(char* stage, int kvalid, int tid) {
   using Cfg = F32DmaCfg<BM, BN, T, BK, TA, TB>;
   asm volatile("" : "+s"(kvalid));   // keeps this rarely run arithmetic out of the stage loop's preheader
+  tid = rarely(tid);
 #pragma unroll
   for (int op = 0; op < 2; ++op) {
     const bool kmajor = op == 0 ? (TA == 0) : (TB == 1);
@@ -123,22 +124,23 @@ __device__ __forceinline__ float f32_at_mnmajor(const float* t, int k, int col) 
 // this load, which bounds it).  Subtraction with a shift, not v_dot2_f32_bf16,
 // makes the residuals: the dot unit shares the matrix pipe.  32x32 wave blocks
 // (T = 4) split twice as many values per MFMA and gained nothing.
-// 128x128 tiles, BK = 32: 4096^3 NT 1051 -> 750 us (131 -> 183 TFLOP/s), NN
-// 1160 -> 803 us; 2048x1024x1536 batch 16 TN 813 -> 610 us.
+// 128x128 tiles, BK = 32: 4096^3 NT 1051 -> 754 us (131 -> 182 TFLOP/s), NN
+// 1160 -> 758 us; 2048x1024x1536 batch 16 TN 813 -> 595 us.
 //
 // Two kinds of operand do not split: infinities and values that round to
 // infinity in BF16, whose residual is NaN, and values below 2^-110 (a NaN does:
-// its row or column of the product is NaN either way).  A wave that meets
-// either where it shows (a non-finite sum that no NaN explains; a sum below
-// 2^27 times what its operands' pieces may leave out of it, where any left
-// something out: one OR per two values, 2.5 % of the kernel)
-// computes its block again with FP32 MFMAs straight from memory,
-// the next 8 of K on their way while the present ones multiply; a work-group
-// whose first stage already holds an infinity or a value of 2^48 or more
-// (smaller ones cannot overflow) leaves the split out.  4096^3 NT / TN with such
-// values takes 1.20 / 1.46 ms where the first stage shows them, 1.67 / 1.79 ms where
-// a later one does (FP32 kernels 1.04); two at a time from memory it took 4.6.
-// With NaN 0.69 / 0.65.
+// its row or column of the product is NaN either way).  A work-group that
+// meets either where it shows (a non-finite sum that no NaN explains; a sum
+// below 2^27 times what its operands' pieces may leave out of it, where any
+// left something out: one OR per two values, 2.5 % of the kernel) computes its
+// tile again on FP32 MFMAs, through the same stages.  In products of 32 stages
+// or more it leaves the split out when the first stage holds an infinity or a
+// value of 2^62 or more (smaller ones seldom overflow; looking costs 3 % of 16
+// stages).  4096^3 NT / TN with infinities on 128x128 tiles: 0.96 / 1.08 ms where
+// the first stage shows them, 1.75 / 1.79 ms where a later one does (FP32 kernels
+// 1.04; the second pass straight from memory, 8 of K at a time: 1.20 / 1.46 and
+// 1.72 / 1.94); 64x64 tiles 1.73 / 1.82 and 2.84 / 3.02 (from memory, 2 at a time: 5.5).
+// With NaN 0.74 / 0.73.
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 
@@ -180,23 +182,29 @@ struct F32Split {
   static constexpr bool value = T == 8 && BK >= 16;
 };
 
+// Stages from which on a split kernel looks through its first one (SplitFrag).
+constexpr int F32_LOOK_FIRST = 32;
+
 // At least two waves per SIMD for the split kernels: with that register
 // budget the accumulators stay out of the AGPRs (and of copies to and from
-// them).
-template <int T, int BK>
+// them).  Not where it spills in the stage loop: tiles of two waves, 32 deep,
+// both operands M/N-major, have twelve block offsets and 32 single LDS reads a
+// step.
+template <int BM, int BN, int T, int BK, int TA, int TB>
 struct F32DmaOcc {
-  static constexpr int value = F32Split<T, BK>::value ? 2 : 1;
+  static constexpr bool SPILLS = BM * BN == 2 * 64 * 64 && BK == 32 && TA == 1 && TB == 0;
+  static constexpr int value = F32Split<T, BK>::value && !SPILLS ? 2 : 1;
 };
 
 template <int BM, int BN, int T, int BK, int TA, int TB>
 __global__ void __launch_bounds__(BM * BN / (T * T))
-__attribute__((amdgpu_waves_per_eu(F32DmaOcc<T, BK>::value, 8)))
+__attribute__((amdgpu_waves_per_eu(F32DmaOcc<BM, BN, T, BK, TA, TB>::value, 8)))
 gemm_f32_dma_kernel(GemmArgs args) {
   using Cfg = F32DmaCfg<BM, BN, T, BK, TA, TB>;
   constexpr int NS = Cfg::NS;
   constexpr int WT = Cfg::WT;
   __shared__ __attribute__((aligned(16))) char lds[Cfg::LDS_BYTES];
-  __shared__ int leave;   // split kernels: the first stage holds values that may not split
+  __shared__ int leave[2];   // split kernels: the first stage, or a sum, asks for FP32 MFMAs
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -211,8 +219,6 @@ gemm_f32_dma_kernel(GemmArgs args) {
   const int64_t m0 = (int64_t)tm * BM, n0 = (int64_t)tn * BN;
   const int64_t M = args.M, N = args.N, K = args.K;
   DmaSource<Cfg, 4, BM, BN, BK, TA, TB, F32Swz<BM, BN, T, BK>> src;
-  src.init(args, static_cast<const char*>(args.A) + bz * args.sA * 4,
-           static_cast<const char*>(args.B) + bz * args.sB * 4, m0, n0, wave, lane);
 
   auto A_at = [&](const float* t, int m, int k) {
     if constexpr (TA == 0) return f32_at_kmajor<BK>(t, m, k);
@@ -238,39 +244,39 @@ gemm_f32_dma_kernel(GemmArgs args) {
       return f32x4{B_at(t, n, k0), B_at(t, n, k0 + 1), B_at(t, n, k0 + 2), B_at(t, n, k0 + 3)};
   };
 
-  constexpr int NACC = (T == 2) ? 4 : (T == 4) ? 16 : 64;
+  constexpr int NACC = (T == 2) ? 4 : (T == 4) ? 16 : 1;
   constexpr bool SPLIT = F32Split<T, BK>::value;
-  constexpr int SUB = 2;   // 32x32 blocks per wave edge (split kernels)
-  float acc[SPLIT ? 1 : NACC];
+  constexpr int SUB = 2;   // T = 8: 32x32 blocks per wave edge
+  float acc[NACC];
   float total[T == 2 ? 4 : 1] = {};
-  f32x16 sacc[SUB][SUB];
-  float most_a[SUB], most_b[SUB];   // largest magnitude of each row and column
-  uint32_t left = 0u;               // a lower half that is not zero: a value that does not split
-  if constexpr (SPLIT) {
 #pragma unroll
-    for (int i = 0; i < SUB; ++i) {
-      most_a[i] = most_b[i] = 0.f;
+  for (int i = 0; i < NACC; ++i) acc[i] = 0.f;
+  f32x16 sacc[SUB][SUB];   // T = 8
+  auto clear = [&]() {
+#pragma unroll
+    for (int i = 0; i < SUB; ++i)
 #pragma unroll
       for (int j = 0; j < SUB; ++j)
 #pragma unroll
         for (int r = 0; r < 16; ++r) sacc[i][j][r] = 0.f;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < NACC; ++i) acc[i] = 0.f;
-  }
+  };
+  if constexpr (T == 8) clear();
 
   const int nk = (int)((K + BK - 1) / BK);
   const int my_blocks = (wave < Cfg::NBLK % Cfg::WAVES || Cfg::NBLK % Cfg::WAVES == 0)
                             ? Cfg::NW_HI : Cfg::NW_LO;
+  auto start = [&](int wave, int lane) __attribute__((always_inline)) {
+    src.init(args, static_cast<const char*>(args.A) + bz * args.sA * 4,
+             static_cast<const char*>(args.B) + bz * args.sB * 4, m0, n0, wave, lane);
 #pragma nounroll
-  for (int s = 0; s < NS - 1; ++s)
-    if (s < nk) src.issue(args, m0, n0, lds0 + s * Cfg::STAGE);
+    for (int s = 0; s < NS - 1; ++s)
+      if (s < nk) src.issue(args, m0, n0, lds0 + s * Cfg::STAGE);
+  };
 
   // Make stage kt readable: its DMA has landed for every wave, K beyond the
   // product is zero, and the stage AHEAD stages on is on its way into the
   // buffer that every wave has finished reading.
-  auto open_stage = [&](int kt, int issued, int ahead_max) {
+  auto open_stage = [&](int kt, int issued, int ahead_max) __attribute__((always_inline)) {
     const int ahead = min(ahead_max, nk - 1 - kt);
     if (my_blocks == Cfg::NW_HI) wait_stage<Cfg::NW_HI, NS>(ahead);
     else wait_stage<Cfg::NW_LO, NS>(ahead);
@@ -283,14 +289,18 @@ gemm_f32_dma_kernel(GemmArgs args) {
     }
     if (issued < nk) src.issue(args, m0, n0, lds0 + (issued % NS) * Cfg::STAGE);
   };
-  bool again = false;   // split kernels: FP32 MFMAs from memory
-  if constexpr (SPLIT) {
+  // The product on the BF16 matrix cores; false where it has to be done with
+  // FP32 MFMAs instead (for the whole work-group alike, which is then done
+  // with its LDS).
+  auto split_product = [&]() __attribute__((always_inline)) {
     // 32x32x16 MFMAs: lane half h takes k = h * BK / 2 + 8 s .. + 7 at step s.
     // The fragments of step g + 1 are read and split while the MFMAs of step
     // g run.
     constexpr int S = BK / 16;   // steps per stage
     const int r32 = lane & 31, h = lane >> 5;
     const int steps = nk * S;
+    float most_a[SUB] = {0.f, 0.f}, most_b[SUB] = {0.f, 0.f};   // largest magnitude of each row and column
+    uint32_t left = 0u;   // a lower half that is not zero: a value that does not split
     struct Frags { SplitFrag a[SUB], b[SUB]; };
     Frags f0, f1;
     f32x4 xa[SUB][2], xb[SUB][2];
@@ -322,7 +332,7 @@ gemm_f32_dma_kernel(GemmArgs args) {
     };
     constexpr int NM = 6 * SUB * SUB, NP = 8 * SUB;
     constexpr int LEAD = NM - NP > 0 ? NM - NP : 0;   // MFMAs over the latency of the reads
-    auto step = [&](const Frags& cur, Frags& next, int g) {
+    auto step = [&](const Frags& cur, Frags& next, int g) __attribute__((always_inline)) {
       if (g % S == 0) open_stage(g / S, g / S + NS - 1, NS - 2);
       fetch(g);
       __builtin_amdgcn_sched_barrier(0);
@@ -344,9 +354,20 @@ gemm_f32_dma_kernel(GemmArgs args) {
 #pragma unroll
       for (int u = 0; u < NM; ++u) mfma(cur, u);
     };
-    if constexpr (Cfg::WAVES >= 4) {
-      if (tid == 0) leave = 0;
-      open_stage(0, NS - 1, NS - 2);
+    // true in every wave when one of them says so
+    auto any_wave = [&](bool v, int flag) __attribute__((always_inline)) {
+      if constexpr (Cfg::WAVES == 1) {
+        return (bool)__any(v);
+      } else {
+        if (__any(v) && lane == 0) leave[flag] = 1;
+        vm_wait_barrier<63>();   // the flag; transfers stay in flight
+        return __builtin_amdgcn_readfirstlane(leave[flag]) != 0;
+      }
+    };
+    if (Cfg::WAVES > 1 && tid == 0) leave[0] = leave[1] = 0;
+    open_stage(0, NS - 1, NS - 2);
+    fetch(0);
+    if (nk >= F32_LOOK_FIRST) {
       // only rows and columns of the product count (below, too): beyond them
       // lies whatever the operands' memory holds
       bool large = false;
@@ -361,40 +382,88 @@ gemm_f32_dma_kernel(GemmArgs args) {
             ma = largest(ma, __builtin_fabsf(xa[i][e / 4][e % 4]));
             mb = largest(mb, __builtin_fabsf(xb[i][e / 4][e % 4]));
           }
-          large = large || (32 * i + r32 < M - m0 - wm0 && ma >= 0x1p48f) ||
-                  (32 * i + r32 < N - n0 - wn0 && mb >= 0x1p48f);
+          large = large || (32 * i + r32 < M - m0 - wm0 && ma >= 0x1p62f) ||
+                  (32 * i + r32 < N - n0 - wn0 && mb >= 0x1p62f);
         }
       }
-      if (__any(large) && lane == 0) leave = 1;
-      vm_wait_barrier<63>();   // the flag; transfers stay in flight
-      again = __builtin_amdgcn_readfirstlane(leave) != 0;
-      if (again) vm_wait_barrier<0>();   // nothing may land in LDS that is no longer ours
-    }
-    if (nk > 0 && !again) {
-      if constexpr (Cfg::WAVES < 4) {
-        open_stage(0, NS - 1, NS - 2);
-        fetch(0);
+      if (any_wave(large, 0)) {
+        vm_wait_barrier<0>();
+        return false;
       }
+    }
 #pragma unroll
-      for (int u = 0; u < NP; ++u) split(f0, u);
-      int g = 0;
-      for (; g + 2 < steps; g += 2) {
-        step(f0, f1, g + 1);
-        step(f1, f0, g + 2);
-      }
-      if (g + 1 < steps) {
-        step(f0, f1, g + 1);
-        last(f1);
-      } else {
-        last(f0);
-      }
+    for (int u = 0; u < NP; ++u) split(f0, u);
+    int g = 0;
+    for (; g + 2 < steps; g += 2) {
+      step(f0, f1, g + 1);
+      step(f1, f0, g + 2);
     }
-  }
+    if (g + 1 < steps) {
+      step(f0, f1, g + 1);
+      last(f1);
+    } else {
+      last(f0);
+    }
+    float nan = 0.f;   // becomes NaN when a sum is not finite
+    bool redo = false;
+    const int rows = (int)min(M - m0 - wm0, (int64_t)(32 * SUB)), cols = (int)min(N - n0 - wn0, (int64_t)(32 * SUB));
+    // Rows and columns that are stored and hold no NaN (where one does, every
+    // output is NaN in any arithmetic): of rows a mask, of columns the lane's own.
+    uint32_t rows_in[SUB];
+    bool col_in[SUB];
+    float row_most[SUB], col_most[SUB];
+#pragma unroll
+    for (int i = 0; i < SUB; ++i) {
+      // both lane halves hold K positions of row / column r32
+      row_most[i] = largest(most_a[i], __shfl_xor(most_a[i], 32));
+      col_most[i] = largest(most_b[i], __shfl_xor(most_b[i], 32));
+      col_in[i] = 32 * i + r32 < cols && col_most[i] == col_most[i];
+      rows_in[i] = (uint32_t)__ballot(32 * i + r32 < rows && row_most[i] == row_most[i]) >> (4 * h);
+    }
+#pragma unroll
+    for (int i = 0; i < SUB; ++i)
+#pragma unroll
+      for (int j = 0; j < SUB; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const bool in = col_in[j] && (rows_in[i] >> ((r >> 2) * 8 + (r & 3)) & 1u) != 0u;
+          nan = fmaf(in ? sacc[i][j][r] : 0.f, 0.f, nan);
+        }
+    if (__any((left & 0xffffu) != 0u)) {
+      // what the pieces leave out of a sum is at most 2^-134 K (row_most + col_most)
+      const float unit = (float)K * 0x1p-107f;
+#pragma unroll
+      for (int i = 0; i < SUB; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int row = (r >> 2) * 8 + (r & 3);
+          const float m = __shfl(row_most[i], row + 4 * h);
+#pragma unroll
+          for (int j = 0; j < SUB; ++j)
+            redo = redo || (col_in[j] && (rows_in[i] >> row & 1u) != 0u && m > 0.f && col_most[j] > 0.f &&
+                            !(__builtin_fabsf(sacc[i][j][r]) >= unit * (m + col_most[j])));
+        }
+    }
+    return !any_wave(redo || nan != nan, 1);
+  };
   // T = 2 carries its running sums to `total` every 256 of K: a chain of K / 4
   // rounded additions is what deep products lose most by (1021 x 515 x 997:
   // 5.6e-7 against 64 bits in one chain, 2.9e-7 in blocks).
   constexpr int SUM_STAGES = T == 2 ? 256 / BK : INT_MAX;
-  for (int kt = 0; kt < (SPLIT ? 0 : nk);) {
+  start(wave, lane);
+  bool done = false;
+  int lane_f = lane, wave_f = wave;
+  if constexpr (SPLIT) {
+    done = split_product();
+    // the second pass works out its addresses by itself: shared with the first
+    // they would have to stay in registers through it
+    asm volatile("" : "+v"(lane_f), "+s"(wave_f));
+    if (!done) {
+      clear();
+      start(wave_f, lane_f);
+    }
+  }
+  for (int kt = done ? nk : 0; kt < nk;) {
     const int end = T == 2 ? min(nk, kt + SUM_STAGES) : nk;
     for (; kt < end; ++kt) {
       open_stage(kt, kt + NS - 1, NS - 2);
@@ -439,30 +508,25 @@ gemm_f32_dma_kernel(GemmArgs args) {
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = c[r];
       } else {
-        const int r32 = lane & 31, h = lane >> 5;
+        const int r32 = lane_f & 31, h = lane_f >> 5;
         constexpr int KH = BK / 2;
-        f32x16 c00, c01, c10, c11;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          c00[r] = acc[r]; c01[r] = acc[16 + r]; c10[r] = acc[32 + r]; c11[r] = acc[48 + r];
-        }
         static_assert(KH % 4 == 0, "whole 16-byte chunks per lane half");
-#pragma unroll
-        for (int q0 = 0; q0 < KH; q0 += 4) {
-          const int k = h * KH + q0;
+        auto group = [&](int k) __attribute__((always_inline)) {
+          const int wm0 = (wave_f / Cfg::Base::WAVES_N) * WT, wn0 = (wave_f % Cfg::Base::WAVES_N) * WT;
           const f32x4 a0 = A4(as, wm0 + r32, k), a1 = A4(as, wm0 + 32 + r32, k);
           const f32x4 b0 = B4(bs, wn0 + r32, k), b1 = B4(bs, wn0 + 32 + r32, k);
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
-            c00 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b0[u], c00, 0, 0, 0);
-            c01 = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b1[u], c01, 0, 0, 0);
-            c10 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b0[u], c10, 0, 0, 0);
-            c11 = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b1[u], c11, 0, 0, 0);
+            sacc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b0[u], sacc[0][0], 0, 0, 0);
+            sacc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b1[u], sacc[0][1], 0, 0, 0);
+            sacc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b0[u], sacc[1][0], 0, 0, 0);
+            sacc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b1[u], sacc[1][1], 0, 0, 0);
           }
-        }
+        };
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          acc[r] = c00[r]; acc[16 + r] = c01[r]; acc[32 + r] = c10[r]; acc[48 + r] = c11[r];
+        for (int q0 = 0; q0 < KH; q0 += 4) {
+          if constexpr (SPLIT) __builtin_amdgcn_sched_barrier(0);   // no more registers than the first pass
+          group(h * KH + q0);
         }
       }
     }
@@ -496,130 +560,7 @@ gemm_f32_dma_kernel(GemmArgs args) {
         for (int r = 0; r < 16; ++r)
           put(32 * i + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), 32 * j + (lane & 31), c[i][j][r]);
   };
-  if constexpr (SPLIT) {
-    const int r32 = lane & 31, h = lane >> 5;
-    float nan = 0.f;   // becomes NaN when a sum is not finite
-    bool redo = false;
-    const int rows = (int)min(M - m0 - wm0, (int64_t)(32 * SUB)), cols = (int)min(N - n0 - wn0, (int64_t)(32 * SUB));
-    // Rows and columns that are stored and hold no NaN (where one does, every
-    // output is NaN in any arithmetic): of rows a mask, of columns the lane's own.
-    uint32_t rows_in[SUB];
-    bool col_in[SUB];
-    float row_most[SUB], col_most[SUB];
-#pragma unroll
-    for (int i = 0; i < SUB; ++i) {
-      // both lane halves hold K positions of row / column r32
-      row_most[i] = largest(most_a[i], __shfl_xor(most_a[i], 32));
-      col_most[i] = largest(most_b[i], __shfl_xor(most_b[i], 32));
-      col_in[i] = 32 * i + r32 < cols && col_most[i] == col_most[i];
-      rows_in[i] = (uint32_t)__ballot(32 * i + r32 < rows && row_most[i] == row_most[i]) >> (4 * h);
-    }
-#pragma unroll
-    for (int i = 0; i < SUB; ++i)
-#pragma unroll
-      for (int j = 0; j < SUB; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const bool in = col_in[j] && (rows_in[i] >> ((r >> 2) * 8 + (r & 3)) & 1u) != 0u;
-          nan = fmaf(in ? sacc[i][j][r] : 0.f, 0.f, nan);
-        }
-    if (__any((left & 0xffffu) != 0u)) {
-      // what the pieces leave out of a sum is at most 2^-134 K (row_most + col_most)
-      const float unit = (float)K * 0x1p-107f;
-#pragma unroll
-      for (int i = 0; i < SUB; ++i)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int row = (r >> 2) * 8 + (r & 3);
-          const float m = __shfl(row_most[i], row + 4 * h);
-#pragma unroll
-          for (int j = 0; j < SUB; ++j)
-            redo = redo || (col_in[j] && (rows_in[i] >> row & 1u) != 0u && m > 0.f && col_most[j] > 0.f &&
-                            !(__builtin_fabsf(sacc[i][j][r]) >= unit * (m + col_most[j])));
-        }
-    }
-    if (again || __any(redo || nan != nan)) {   // wave-uniform
-      const float* Af = static_cast<const float*>(args.A) + bz * args.sA;
-      const float* Bf = static_cast<const float*>(args.B) + bz * args.sB;
-      const float *pa[SUB], *pb[SUB];
-      f32x16 c[SUB][SUB];
-#pragma unroll
-      for (int i = 0; i < SUB; ++i) {
-        pa[i] = Af + min(m0 + wm0 + 32 * i + r32, M - 1) * (TA == 0 ? args.lda : 1);
-        pb[i] = Bf + min(n0 + wn0 + 32 * i + r32, N - 1) * (TB == 1 ? args.ldb : 1);
-#pragma unroll
-        for (int j = 0; j < SUB; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) c[i][j][r] = 0.f;
-      }
-      const int64_t ka = TA == 0 ? 1 : args.lda, kb = TB == 1 ? 1 : args.ldb;
-      int64_t whole = 0;   // K done below, eight at a time
-      // (smaller work-groups' kernels have no registers to spare for it)
-      if constexpr (Cfg::WAVES >= 4) {
-        typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-        struct Eight { float a[SUB][4], b[SUB][4]; };   // half h: k0 + 4 h .. + 3
-        auto get = [&](float (&x)[4], const float* p, int64_t ld, bool kmajor) {
-          if (kmajor) {
-            const f32x4u v = *reinterpret_cast<const f32x4u*>(p);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) x[e] = v[e];
-          } else {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) x[q] = p[q * ld];
-          }
-        };
-        auto load = [&](Eight& x, int64_t k0) {
-#pragma unroll
-          for (int i = 0; i < SUB; ++i) {
-            get(x.a[i], pa[i] + (k0 + 4 * h) * ka, ka, TA == 0);
-            get(x.b[i], pb[i] + (k0 + 4 * h) * kb, kb, TB == 1);
-          }
-        };
-        auto multiply = [&](const Eight& x) {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int i = 0; i < SUB; ++i)
-#pragma unroll
-              for (int j = 0; j < SUB; ++j)
-                c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(x.a[i][q], x.b[j][q], c[i][j], 0, 0, 0);
-        };
-        whole = K / 8 * 8;
-        Eight x0, x1;
-        load(x0, 0);   // split kernels have K >= 16
-#pragma nounroll
-        for (int64_t k0 = 0; k0 < whole; k0 += 16) {
-          // past the end: the last 8 again, not multiplied
-          load(x1, min(k0 + 8, whole - 8));
-          __builtin_amdgcn_sched_barrier(0);
-          multiply(x0);
-          if (k0 + 8 >= whole) break;
-          load(x0, min(k0 + 16, whole - 8));
-          __builtin_amdgcn_sched_barrier(0);
-          multiply(x1);
-        }
-      }
-#pragma nounroll
-      for (int64_t k0 = whole; k0 < K; k0 += 2) {
-        const int64_t k = k0 + h;
-        float a[SUB], b[SUB];
-#pragma unroll
-        for (int i = 0; i < SUB; ++i) {
-          a[i] = k < K ? pa[i][k * ka] : 0.f;
-          b[i] = k < K ? pb[i][k * kb] : 0.f;
-        }
-#pragma unroll
-        for (int i = 0; i < SUB; ++i)
-#pragma unroll
-          for (int j = 0; j < SUB; ++j)
-            c[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], c[i][j], 0, 0, 0);
-      }
-      put_blocks(c);
-      return;
-    }
-  }
-
-  if constexpr (SPLIT) {
+  if constexpr (T == 8) {
     put_blocks(sacc);
   } else if constexpr (T == 2) {
 #pragma unroll
@@ -627,15 +568,6 @@ gemm_f32_dma_kernel(GemmArgs args) {
   } else if constexpr (T == 4) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) put((r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), lane & 31, acc[r]);
-  } else {
-#pragma unroll
-    for (int sub = 0; sub < 4; ++sub) {
-      const int si = sub >> 1, sj = sub & 1;
-#pragma unroll
-      for (int r = 0; r < 16; ++r)
-        put(32 * si + (r >> 2) * 8 + (lane >> 5) * 4 + (r & 3), 32 * sj + (lane & 31),
-            acc[16 * (2 * si + sj) + r]);
-    }
   }
 }
 

@@ -142,6 +142,13 @@ __device__ __forceinline__ int mswz(int k) {
   return ((k / RP) * W) % CPR;
 }
 
+// A lane's value for work that a loop seldom does: what follows from it is
+// worked out there, not ahead of the loop in registers that the loop needs.
+__device__ __forceinline__ int rarely(int v) {
+  asm volatile("" : "+v"(v));
+  return v;
+}
+
 // Where a wave's DMA blocks of one stage come from.  Block q of the stage
 // (0 .. NBA-1: A, then B) is handled by wave q % WAVES; rows / columns beyond
 // the operand are clamped to in-range addresses.
@@ -200,7 +207,7 @@ struct DmaSource {
 
   // Offsets of block i beyond K in the last stage, which holds left_k of it, moved
   // back to its last chunk or row.
-  __device__ __forceinline__ uint32_t in_tail(const GemmArgs& g, int i, int left_k) const {
+  __device__ __forceinline__ uint32_t in_tail(const GemmArgs& g, int i, int left_k, int lane) const {
     bool is_a, kmajor;
     int r, col;
     place(wave + i * Cfg::WAVES, lane, is_a, kmajor, r, col);
@@ -268,20 +275,22 @@ struct DmaSource {
           if (exists(i))
             lds_dma16(of_a(i) ? a : b, off[i], stage + (wave + i * Cfg::WAVES) * 1024);
       } else {
+        const int l = rarely(lane);
 #pragma unroll
         for (int i = 0; i < Cfg::NW_HI; ++i)
           if (exists(i))
             lds_dma16(of_a(i) ? a : b,
-                      EB == 4 ? min(in_tail(g, i, left_k), of_a(i) ? ea : eb) : in_tail(g, i, left_k),
+                      EB == 4 ? min(in_tail(g, i, left_k, l), of_a(i) ? ea : eb) : in_tail(g, i, left_k, l),
                       stage + (wave + i * Cfg::WAVES) * 1024);
       }
     } else {
       // whole addresses: a loop, out of the way of the products that have offsets
+      const int l = rarely(lane);
 #pragma nounroll
       for (int q = wave; q < Cfg::NBLK; q += Cfg::WAVES) {
         bool is_a, kmajor;
         int r, col;
-        place(q, lane, is_a, kmajor, r, col);
+        place(q, l, is_a, kmajor, r, col);
         const int64_t left = is_a ? g.M - m0 : g.N - n0;
         const int64_t ld = is_a ? g.lda : g.ldb;
         int64_t row = r, c = col;
@@ -309,6 +318,7 @@ struct DmaSource {
   __device__ __forceinline__ bool settle(const GemmArgs& g, int64_t m0, int64_t n0, int left_k,
                                          char* stage, int tid) const {
     if (!ragged) return false;
+    tid = rarely(tid);
     if (tid < 2) {   // one thread per operand
       const bool is_a = tid == 0, kmajor = is_a ? (TA == 0) : (TB == 1);
       const int64_t left = is_a ? g.M - m0 : g.N - n0;
@@ -340,6 +350,7 @@ __device__ __forceinline__ void lp_dma_zero_tail(char* stage, int kvalid, int ti
   using Cfg = LpDmaCfg<EB, BM, BN, T, BK, TA, TB>;
   typedef typename LpElem<EB>::T E;
   asm volatile("" : "+s"(kvalid));   // keeps this rarely run arithmetic out of the stage loop's preheader
+  tid = rarely(tid);
 #pragma unroll
   for (int op = 0; op < 2; ++op) {
     const bool kmajor = op == 0 ? (TA == 0) : (TB == 1);
