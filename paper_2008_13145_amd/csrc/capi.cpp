@@ -176,9 +176,17 @@ kt_status kt_create(kt_handle* out, int device) {
   h->device = device;
   build_tables(h);
   if (device >= 0) {
+    // here, while the handle's device is the current one: an event is recorded
+    // on streams of the device it was created on only
+    hipError_t e = hipEventCreateWithFlags(&h->deep_done, hipEventDisableTiming | hipEventDisableSystemFence);
+    if (e != hipSuccess) {
+      delete h;
+      return fail(nullptr, KT_EHIP, std::string("workspace event: ") + hipGetErrorString(e));
+    }
     kt_status st = noalloc_scratch_init(h);
     if (st != KT_OK) {
       g_create_err = h->err;
+      (void)hipEventDestroy(h->deep_done);
       delete h;
       return st;
     }
@@ -258,10 +266,6 @@ kt_status kt_set_workspace(kt_handle hh, void* workspace, size_t bytes) {
   Ctx* h = reinterpret_cast<Ctx*>(hh);
   if (!h) return fail(nullptr, KT_EINVAL, "NULL handle");
   if (!workspace && bytes) return fail(h, KT_EINVAL, "NULL workspace with a nonzero size");
-  if (h->device >= 0 && workspace && !h->deep_done) {
-    hipError_t e = hipEventCreateWithFlags(&h->deep_done, hipEventDisableTiming | hipEventDisableSystemFence);
-    if (e != hipSuccess) { h->deep_done = nullptr; return hip_fail(h, e, "workspace event"); }
-  }
   h->gemm_ws = workspace;
   h->gemm_ws_bytes = workspace ? bytes : 0;
   if (!workspace) return KT_OK;

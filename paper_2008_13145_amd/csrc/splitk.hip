@@ -172,7 +172,7 @@ kt_status run_deep(Ctx* h, kt_dtype dtype, const kt_shape* s, float alpha, const
   *ran = false;
   const int32_t slices = deep_slices(h, dtype, s, id);
   const size_t planes = split_plane_bytes(s, slices);
-  if (planes == 0 || !h->gemm_ws || h->gemm_ws_bytes < planes || !h->deep_done) return KT_OK;
+  if (planes == 0 || !h->gemm_ws || h->gemm_ws_bytes < planes) return KT_OK;
   const size_t off = (h->gemm_ws_bytes - planes) & ~(size_t)255;
   char* at = (char*)h->gemm_ws + off;
   if (off < h->ws_low) return KT_OK;
