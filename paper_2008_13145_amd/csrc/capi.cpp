@@ -79,24 +79,15 @@ kt_status check_gemm_args(Ctx* h, const kt_shape* s, int64_t lda, int64_t sA, in
 
 static int elem_bytes(int dtype) { return dtype == KT_F32 ? 4 : dtype == KT_BF16 ? 2 : 1; }
 
-// Row alignment of an operand for the low-precision loaders: 2 = every row
-// starts on a 4-byte boundary, 1 = only the base pointer does (rows are then
-// loaded through a realigned window), 0 = neither (element loads); 3 = every
-// row on a 16-byte boundary and whole 16-byte chunks along the contiguous
-// extent `ext` (K for an operand stored K-contiguous, M or N otherwise),
-// which takes the DMA pipeline.
-int32_t operand_alignment(int dtype, const void* p, int64_t ld, int64_t stride, int64_t batch,
-                          int64_t ext, bool full_rows) {
+RowAlign operand_alignment(int dtype, const void* p, int64_t ld, int64_t stride, int64_t batch,
+                           int64_t ext, bool full_rows) {
   const int eb = elem_bytes(dtype);
-  if ((uintptr_t)p % 4 != 0) return 0;
-  if ((ld * eb) % 4 != 0 || (stride * eb) % 4 != 0) return 1;
+  if ((uintptr_t)p % 4 != 0 || (ld * eb) % 4 != 0 || (stride * eb) % 4 != 0) return ROWS_ANY;
   const int64_t ce = 16 / eb;
-  // with rows allocated in full, a row's last chunk may end anywhere within
-  // the leading dimension
   const bool ext_ok = ext % ce == 0 || (full_rows && ext >= ce && ld >= (ext + ce - 1) / ce * ce);
   if ((uintptr_t)p % 16 == 0 && ld % ce == 0 && (batch <= 1 || stride % ce == 0) && ext_ok)
-    return 3;
-  return 2;
+    return ROWS_16;
+  return ROWS_4;
 }
 
 kt_status launch_gemm(Ctx* h, int dtype, const kt_shape* s, float alpha, const void* A,
@@ -119,8 +110,8 @@ kt_status launch_gemm(Ctx* h, int dtype, const kt_shape* s, float alpha, const v
   g.lda = lda; g.sA = sA; g.ldb = ldb; g.sB = sB; g.ldc = ldc; g.sC = sC;
   g.alpha = alpha; g.beta = beta;
   g.scaleA = scaleA; g.scaleB = scaleB;
-  g.vecA = operand_alignment(dtype, A, lda, sA, s->batch, s->transA ? s->M : s->K, h->full_rows);
-  g.vecB = operand_alignment(dtype, B, ldb, sB, s->batch, s->transB ? s->K : s->N, h->full_rows);
+  g.alignA = operand_alignment(dtype, A, lda, sA, s->batch, s->transA ? s->M : s->K, h->full_rows);
+  g.alignB = operand_alignment(dtype, B, ldb, sB, s->batch, s->transB ? s->K : s->N, h->full_rows);
   g.batch = s->batch;
   g.A = A;
   g.B = B;
@@ -351,9 +342,9 @@ kt_status kt_dma_pipeline(kt_handle hh, kt_dtype dtype, const kt_shape* s, const
   if (!s || !dma) return fail(h, KT_EINVAL, "NULL argument");
   if ((int)dtype < 0 || (int)dtype >= NUM_DTYPES) return fail(h, KT_EINVAL, "bad dtype");
   *dma = operand_alignment(dtype, A, lda, strideA, s->batch, s->transA ? s->M : s->K,
-                           h->full_rows) == 3 &&
+                           h->full_rows) == ROWS_16 &&
          operand_alignment(dtype, B, ldb, strideB, s->batch, s->transB ? s->K : s->N,
-                           h->full_rows) == 3;
+                           h->full_rows) == ROWS_16;
   return KT_OK;
 }
 

@@ -41,6 +41,11 @@ struct FastDiv {
   }
 };
 
+// Where the rows of an operand start, all batch items included: anywhere; on
+// 4-byte boundaries; on 16-byte boundaries with no 16-byte chunk read leaving
+// the operand (operand_alignment).
+enum RowAlign : int32_t { ROWS_ANY, ROWS_4, ROWS_16 };
+
 struct GemmArgs {
   int64_t M, N, K, batch;
   const void* A; int64_t lda, sA;
@@ -48,13 +53,13 @@ struct GemmArgs {
   float* C; int64_t ldc, sC;
   float alpha, beta;
   const float* scaleA; const float* scaleB;   // FP8 only
-  int32_t vecA, vecB;   // row alignment mode of each operand (LP_ALIGN_*)
-  int32_t ragged;       // FP32 DMA kernels: some operand row is not on a 16-byte boundary
+  int32_t alignA, alignB;   // RowAlign of each operand
+  int32_t ragged;           // FP32 DMA kernels: some operand row is not on a 16-byte boundary
   int32_t tiles_m, tiles_n;
-  uint32_t blocks;      // tiles_m * tiles_n * batch of this launch
-  FastDiv per_item;     // by tiles_m * tiles_n
-  FastDiv per_group;    // by 8 * tiles_n
-  FastDiv last_rows;    // by the tile rows of the last group of 8
+  uint32_t blocks;          // tiles_m * tiles_n * batch of this launch
+  FastDiv per_item;         // by tiles_m * tiles_n
+  FastDiv per_group;        // by 8 * tiles_n
+  FastDiv last_rows;        // by the tile rows of the last group of 8
 };
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));

@@ -602,10 +602,10 @@ template <int BM, int BN, int T, int BK, int TA, int TB>
 hipError_t launch_gemm_f32(const GemmArgs& a, hipStream_t stream) {
   using Cfg = GemmF32Cfg<BM, BN, T, BK, TA, TB>;
   if constexpr (F32DmaServes<BM, BN, T, BK>::value) {
-    if (a.vecA >= LP_ALIGN_ROWS && a.vecB >= LP_ALIGN_ROWS && a.K >= (F32Split<T, BK>::value ? 16 : 4) &&
+    if (a.alignA >= ROWS_4 && a.alignB >= ROWS_4 && a.K >= (F32Split<T, BK>::value ? 16 : 4) &&
         (TA == 0 || a.M >= 4) && (TB == 1 || a.N >= 4)) {
       GemmArgs g = a;
-      g.ragged = a.vecA != LP_ALIGN_DMA || a.vecB != LP_ALIGN_DMA;
+      g.ragged = a.alignA != ROWS_16 || a.alignB != ROWS_16;
       if (!g.ragged || a.K >= F32DenseK<T, BK>::value)
         return launch_flat<4>(gemm_f32_dma_kernel<BM, BN, T, BK, TA, TB>, g, BM, BN, Cfg::NT, stream);
     }

@@ -26,9 +26,7 @@ namespace kt {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
-typedef int i32x8a16 __attribute__((ext_vector_type(8), aligned(16)));
 
 template <int EB>   // element bytes: 2 = BF16, 1 = FP8 e4m3
 struct LpElem;
@@ -36,11 +34,6 @@ template <>
 struct LpElem<2> { typedef uint16_t T; static constexpr int KSTEP = 16, KSTEP16 = 32; };
 template <>
 struct LpElem<1> { typedef uint8_t T; static constexpr int KSTEP = 64, KSTEP16 = 128; };
-
-// Operand alignment modes (GemmArgs::vecA / vecB): 2 = every row starts on a
-// 4-byte boundary; 1 = only the operand's base does (odd leading dimension or
-// batch stride); 0 = unaligned base.
-enum { LP_ALIGN_NONE = 0, LP_ALIGN_BASE = 1, LP_ALIGN_ROWS = 2 };
 
 template <int EB, int BM, int BN, int T, int BK, int TA, int TB>
 struct GemmLpCfg {
@@ -60,19 +53,13 @@ struct GemmLpCfg {
 };
 
 // One lane's operand fragment for one MFMA: 8 BF16 values (16 bytes) or
-// 32 FP8 codes (32 bytes), read from LDS as one or two 16-byte reads.
+// 32 FP8 codes (32 bytes).
 template <int EB>
 struct LpFrag;
 template <>
-struct LpFrag<2> {
-  bf16x8 v;
-  __device__ __forceinline__ void read(const void* p) { v = *reinterpret_cast<const bf16x8*>(p); }
-};
+struct LpFrag<2> { bf16x8 v; };
 template <>
-struct LpFrag<1> {
-  i32x8 v;
-  __device__ __forceinline__ void read(const void* p) { v = *reinterpret_cast<const i32x8a16*>(p); }
-};
+struct LpFrag<1> { i32x8 v; };
 
 __device__ __forceinline__ void lp_mfma(const LpFrag<2>& a, const LpFrag<2>& b, f32x16& c) {
   c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a.v, b.v, c, 0, 0, 0);

@@ -31,9 +31,6 @@
 
 namespace kt {
 
-// GemmArgs::vecA / vecB value for rows on 16-byte boundaries.
-enum { LP_ALIGN_DMA = 3 };
-
 typedef __attribute__((address_space(3))) void lds_void_t;
 typedef __attribute__((address_space(1))) void gbl_void_t;
 typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -383,7 +380,7 @@ __device__ __forceinline__ void lp_frag_kmajor(LpFrag<EB>& f, const char* tile, 
   const int c = (s * KSTEP + kh) * EB / 16;
   const char* rp = tile + row * (BK * EB);
   if constexpr (EB == 2) {
-    f.read(rp + (c ^ kswz<CPR>(row)) * 16);
+    f.v = *reinterpret_cast<const bf16x8*>(rp + (c ^ kswz<CPR>(row)) * 16);
   } else {
     const u32x4 lo = *reinterpret_cast<const u32x4*>(rp + (c ^ kswz<CPR>(row)) * 16);
     const u32x4 hi = *reinterpret_cast<const u32x4*>(rp + ((c + 1) ^ kswz<CPR>(row)) * 16);
@@ -724,7 +721,7 @@ gemm_lp_dma_kernel(GemmArgs args) {
 template <int EB, int BM, int BN, int T, int BK, int TA, int TB>
 hipError_t launch_gemm_lp(const GemmArgs& a, hipStream_t stream) {
   using Cfg = GemmLpCfg<EB, BM, BN, T, BK, TA, TB>;
-  if (a.vecA == LP_ALIGN_DMA && a.vecB == LP_ALIGN_DMA)
+  if (a.alignA == ROWS_16 && a.alignB == ROWS_16)
     return launch_flat<EB>(gemm_lp_dma_kernel<EB, BM, BN, T, BK, TA, TB>, a, BM, BN, Cfg::NT,
                            stream);
   return launch_flat<EB>(gemm_lp_kernel<EB, BM, BN, T, BK, TA, TB>, a, BM, BN, Cfg::NT, stream);

@@ -115,7 +115,8 @@ grouped_bf16_kernel(const GroupDesc* __restrict__ descs, const WorkItem* __restr
     a.C = d.C; a.ldc = d.ldc; a.sC = 0;
     a.alpha = alpha; a.beta = beta;
     a.scaleA = nullptr; a.scaleB = nullptr;
-    a.vecA = a.vecB = a.ragged = 0;
+    a.alignA = a.alignB = ROWS_ANY;
+    a.ragged = 0;
     a.tiles_m = 0; a.tiles_n = 0;
     if constexpr (TWO) {
       if (it.cls == 0) Big::run(a, it.tm, it.tn, d.dma != 0, lds);

@@ -99,9 +99,12 @@ kt_status launch_gemm(Ctx* h, int dtype, const kt_shape* s, float alpha, const v
                       float beta, float* C, int64_t ldc, int64_t sC, const float* scaleA,
                       const float* scaleB, int32_t cfg, hipStream_t stream);
 
-// Alignment class of an operand (GemmArgs::vecA / vecB).
-int32_t operand_alignment(int dtype, const void* p, int64_t ld, int64_t stride, int64_t batch,
-                          int64_t ext, bool full_rows);
+// Where an operand's rows start (GemmArgs::alignA / alignB).  ROWS_16 also asks
+// that its contiguous extent `ext` (K for an operand stored K-contiguous, M or
+// N otherwise) is whole 16-byte chunks or, with rows allocated in full, that
+// the last one ends within the leading dimension.
+RowAlign operand_alignment(int dtype, const void* p, int64_t ld, int64_t stride, int64_t batch,
+                           int64_t ext, bool full_rows);
 
 // Kernel ids: configurations 0 .. n_configs-1, then split-K variants.
 inline int32_t num_kernels(const Ctx* h, int dtype) {
