@@ -141,6 +141,8 @@ __device__ __forceinline__ int mswz(int k) {
 
 // A lane's value for work that a loop seldom does: what follows from it is
 // worked out there, not ahead of the loop in registers that the loop needs.
+// FP32 kernels only: low-precision ones have no branches that need it, and
+// BF16 NN on (256, 256, 8, 64) spilled with it.
 __device__ __forceinline__ int rarely(int v) {
   asm volatile("" : "+v"(v));
   return v;
@@ -190,6 +192,8 @@ struct DmaSource {
       col = (((o % rowb) / 16) ^ (is_a ? Swz::mn_a(r) : Swz::mn_b(r))) * CE;
     }
   }
+
+  __device__ __forceinline__ static int seldom(int v) { return EB == 4 ? rarely(v) : v; }
 
   // Whether block i of every wave exists, and whether it is one of A's for
   // every wave / for none; only where the blocks do not divide evenly is
@@ -272,7 +276,7 @@ struct DmaSource {
           if (exists(i))
             lds_dma16(of_a(i) ? a : b, off[i], stage + (wave + i * Cfg::WAVES) * 1024);
       } else {
-        const int l = rarely(lane);
+        const int l = seldom(lane);
 #pragma unroll
         for (int i = 0; i < Cfg::NW_HI; ++i)
           if (exists(i))
@@ -282,7 +286,7 @@ struct DmaSource {
       }
     } else {
       // whole addresses: a loop, out of the way of the products that have offsets
-      const int l = rarely(lane);
+      const int l = seldom(lane);
 #pragma nounroll
       for (int q = wave; q < Cfg::NBLK; q += Cfg::WAVES) {
         bool is_a, kmajor;
@@ -347,7 +351,6 @@ __device__ __forceinline__ void lp_dma_zero_tail(char* stage, int kvalid, int ti
   using Cfg = LpDmaCfg<EB, BM, BN, T, BK, TA, TB>;
   typedef typename LpElem<EB>::T E;
   asm volatile("" : "+s"(kvalid));   // keeps this rarely run arithmetic out of the stage loop's preheader
-  tid = rarely(tid);
 #pragma unroll
   for (int op = 0; op < 2; ++op) {
     const bool kmajor = op == 0 ? (TA == 0) : (TB == 1);
