@@ -463,72 +463,82 @@ gemm_f32_dma_kernel(GemmArgs args) {
       start(wave_f, lane_f);
     }
   }
+  // The products of the stage held at `cur`.
+  auto products = [&](const char* cur) __attribute__((always_inline)) {
+    const float* as = reinterpret_cast<const float*>(cur);
+    const float* bs = reinterpret_cast<const float*>(cur + Cfg::A_BYTES);
+    if constexpr (T == 2) {
+      // 16x16x4: lane quarter g = lane / 16 takes k = g * BK / 4 + q
+      const int r16 = lane & 15, g = lane >> 4;
+      constexpr int KQ = BK / 4;
+      f32x4 c = {acc[0], acc[1], acc[2], acc[3]};
+      // element reads, which the compiler merges where it can (explicit
+      // 16-byte reads measured 3 % slower here on the mixed layouts); 64 deep,
+      // all in flight before the first MFMA (left to the scheduler, each
+      // MFMA group waited for its own: 1021x515x997 NT 54.6 -> 50.6 us, 4 x
+      // 1x4096x6272 81 -> 75 us on (32, 32, 2, 64); 32 deep it gains nothing)
+      float a[KQ], b[KQ];
+#pragma unroll
+      for (int q = 0; q < KQ; ++q) {
+        a[q] = A_at(as, wm0 + r16, g * KQ + q);
+        b[q] = B_at(bs, wn0 + r16, g * KQ + q);
+      }
+      if (BK >= 64) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < KQ; ++q) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[q], c, 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] = c[r];
+    } else if constexpr (T == 4) {
+      const int r32 = lane & 31, h = lane >> 5;
+      constexpr int KH = BK / 2;
+      f32x16 c;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) c[r] = acc[r];
+      static_assert(KH % 4 == 0, "whole 16-byte chunks per lane half");
+#pragma unroll
+      for (int q0 = 0; q0 < KH; q0 += 4) {
+        const f32x4 a = A4(as, wm0 + r32, h * KH + q0);
+        const f32x4 b = B4(bs, wn0 + r32, h * KH + q0);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], c, 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[r] = c[r];
+    } else {
+      const int r32 = lane_f & 31, h = lane_f >> 5;
+      constexpr int KH = BK / 2;
+      static_assert(KH % 4 == 0, "whole 16-byte chunks per lane half");
+      auto group = [&](int k) __attribute__((always_inline)) {
+        const int wm0 = (wave_f / Cfg::Base::WAVES_N) * WT, wn0 = (wave_f % Cfg::Base::WAVES_N) * WT;
+        const f32x4 a0 = A4(as, wm0 + r32, k), a1 = A4(as, wm0 + 32 + r32, k);
+        const f32x4 b0 = B4(bs, wn0 + r32, k), b1 = B4(bs, wn0 + 32 + r32, k);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          sacc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b0[u], sacc[0][0], 0, 0, 0);
+          sacc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b1[u], sacc[0][1], 0, 0, 0);
+          sacc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b0[u], sacc[1][0], 0, 0, 0);
+          sacc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b1[u], sacc[1][1], 0, 0, 0);
+        }
+      };
+#pragma unroll
+      for (int q0 = 0; q0 < KH; q0 += 4) {
+        if constexpr (SPLIT) __builtin_amdgcn_sched_barrier(0);   // no more registers than the first pass
+        group(h * KH + q0);
+      }
+    }
+  };
+  const int lean = T == 8 || done ? 0 : src.lean_stages(nk);
   for (int kt = done ? nk : 0; kt < nk;) {
     const int end = T == 2 ? min(nk, kt + SUM_STAGES) : nk;
+    if constexpr (T != 8) {
+      for (const int to = min(end, lean); kt < to; ++kt) {
+        lean_stage<Cfg>(src, kt, my_blocks == Cfg::NW_HI, lds0);
+        products(lds + (uint32_t)kt % NS * Cfg::STAGE);
+      }
+    }
     for (; kt < end; ++kt) {
       open_stage(kt, kt + NS - 1, NS - 2);
-      char* cur = lds + (kt % NS) * Cfg::STAGE;
-      const float* as = reinterpret_cast<const float*>(cur);
-      const float* bs = reinterpret_cast<const float*>(cur + Cfg::A_BYTES);
-      if constexpr (T == 2) {
-        // 16x16x4: lane quarter g = lane / 16 takes k = g * BK / 4 + q
-        const int r16 = lane & 15, g = lane >> 4;
-        constexpr int KQ = BK / 4;
-        f32x4 c = {acc[0], acc[1], acc[2], acc[3]};
-        // element reads, which the compiler merges where it can (explicit
-        // 16-byte reads measured 3 % slower here on the mixed layouts); 64 deep,
-        // all in flight before the first MFMA (left to the scheduler, each
-        // MFMA group waited for its own: 1021x515x997 NT 54.6 -> 50.6 us, 4 x
-        // 1x4096x6272 81 -> 75 us on (32, 32, 2, 64); 32 deep it gains nothing)
-        float a[KQ], b[KQ];
-#pragma unroll
-        for (int q = 0; q < KQ; ++q) {
-          a[q] = A_at(as, wm0 + r16, g * KQ + q);
-          b[q] = B_at(bs, wn0 + r16, g * KQ + q);
-        }
-        if (BK >= 64) __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int q = 0; q < KQ; ++q) c = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[q], c, 0, 0, 0);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = c[r];
-      } else if constexpr (T == 4) {
-        const int r32 = lane & 31, h = lane >> 5;
-        constexpr int KH = BK / 2;
-        f32x16 c;
-#pragma unroll
-        for (int r = 0; r < 16; ++r) c[r] = acc[r];
-        static_assert(KH % 4 == 0, "whole 16-byte chunks per lane half");
-#pragma unroll
-        for (int q0 = 0; q0 < KH; q0 += 4) {
-          const f32x4 a = A4(as, wm0 + r32, h * KH + q0);
-          const f32x4 b = B4(bs, wn0 + r32, h * KH + q0);
-#pragma unroll
-          for (int u = 0; u < 4; ++u) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], c, 0, 0, 0);
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = c[r];
-      } else {
-        const int r32 = lane_f & 31, h = lane_f >> 5;
-        constexpr int KH = BK / 2;
-        static_assert(KH % 4 == 0, "whole 16-byte chunks per lane half");
-        auto group = [&](int k) __attribute__((always_inline)) {
-          const int wm0 = (wave_f / Cfg::Base::WAVES_N) * WT, wn0 = (wave_f % Cfg::Base::WAVES_N) * WT;
-          const f32x4 a0 = A4(as, wm0 + r32, k), a1 = A4(as, wm0 + 32 + r32, k);
-          const f32x4 b0 = B4(bs, wn0 + r32, k), b1 = B4(bs, wn0 + 32 + r32, k);
-#pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            sacc[0][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b0[u], sacc[0][0], 0, 0, 0);
-            sacc[0][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a0[u], b1[u], sacc[0][1], 0, 0, 0);
-            sacc[1][0] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b0[u], sacc[1][0], 0, 0, 0);
-            sacc[1][1] = __builtin_amdgcn_mfma_f32_32x32x2f32(a1[u], b1[u], sacc[1][1], 0, 0, 0);
-          }
-        };
-#pragma unroll
-        for (int q0 = 0; q0 < KH; q0 += 4) {
-          if constexpr (SPLIT) __builtin_amdgcn_sched_barrier(0);   // no more registers than the first pass
-          group(h * KH + q0);
-        }
-      }
+      products(lds + (kt % NS) * Cfg::STAGE);
     }
     if constexpr (T == 2) {
 #pragma unroll
