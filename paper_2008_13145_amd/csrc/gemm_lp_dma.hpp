@@ -675,6 +675,57 @@ struct StagedOperand {
     base += KM ? COLS * EB : ROWS * ld;
   }
 
+  // Chunks i0 .. i0 + G - 1 of the next stage, and their way to LDS; after all
+  // of them, on to the stage behind it.
+  template <int G>
+  __device__ __forceinline__ void fetch(int i0, int64_t left_k, u32x4 (&t)[G]) const {
+    const bool whole = plain && left_k >= (KM ? COLS : ROWS);
+    const int k = (int)min(left_k, (int64_t)(KM ? COLS : ROWS));
+    const uint32_t c = (uint32_t)(edge ? min(col, left - CE) : col) * EB;
+    const int first = rarely(row0);   // no addresses kept from stage to stage
+    if (whole) {
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+        const int r = first + (i0 + u) * STEP;
+        if (NV % (NT * G) == 0 || r < ROWS)
+          t[u] = *reinterpret_cast<const Chunk*>(base + ((uint32_t)(KM ? min(r, left - 1) : r) * (uint32_t)ld + c));
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < G; ++u) {
+        const int r = first + (i0 + u) * STEP;
+        if (NV % (NT * G) == 0 || r < ROWS) t[u] = chunk(r, k);
+        __builtin_amdgcn_sched_barrier(0);   // one chunk's elements at a time
+      }
+    }
+  }
+  template <int G>
+  __device__ __forceinline__ void place(int i0, int64_t left_k, u32x4 (&t)[G], char* tile) const {
+    typedef unsigned __int128 u128;
+    const bool shift = plain && edge && left_k >= ROWS;
+    const int sh = shift ? min(max(col + CE - left, 0) * EB, 15) * 8 : 0;
+    const int first = rarely(row0);
+#pragma unroll
+    for (int u = 0; u < G; ++u) {
+      const int r = first + (i0 + u) * STEP;
+      if (NV % (NT * G) == 0 || r < ROWS) {
+        if (!KM && shift) t[u] = __builtin_bit_cast(u32x4, __builtin_bit_cast(u128, t[u]) >> sh);
+        const int sw = KM ? kswz<CPR>(r) : mswz<CPR, EB == 2 ? 4 : 2>(r);
+        *reinterpret_cast<u32x4*>(tile + r * (COLS * EB) + ((col / CE) ^ sw) * 16) = t[u];
+      }
+    }
+  }
+  template <int G>
+  __device__ __forceinline__ void rest(int64_t left_k, u32x4 (&t)[G], char* tile) {
+    place(0, left_k, t, tile);
+#pragma nounroll
+    for (int i0 = G; i0 < PT; i0 += G) {
+      fetch(i0, left_k, t);
+      place(i0, left_k, t, tile);
+    }
+    base += KM ? COLS * EB : ROWS * ld;
+  }
+
   __device__ __forceinline__ void store(char* tile) {
     if (late) {
       const int sh = min(max(col + CE - left, 0) * EB, 15) * 8;
@@ -714,6 +765,29 @@ __device__ __forceinline__ void lp_tile(const GemmArgs& args, int tm, int tn, in
   LpTileMath<EB, BM, BN, T, BK, TA, TB> math;
   math.init(wave, tid & 63);
   const int nk = (int)((K + BK - 1) / BK);
+  if constexpr (T == 16 && decltype(a)::PT + decltype(b)::PT >= 16) {
+    // 256 accumulators a lane leave room for at most 15 chunks under the products
+    // (16 and more: up to 2.7 KB of scratch memory a lane): these follow them,
+    // eight of each operand in flight.  Dense 8 x 1021x771x515 NN in BF16, (128,
+    // 256, 16, 64): 268 -> 105 us; (256, 256, 16, 32), 8 chunks: 80 us under the
+    // products, 177 after them.
+    for (int kt = -1; kt < nk; ++kt) {
+      const int64_t left_k = K - (int64_t)(kt + 1) * BK;
+      if (kt >= 0) math.stage(lds + (kt & 1) * Cfg::STAGE);
+      __builtin_amdgcn_sched_barrier(0);
+      if (left_k > 0) {
+        char* next = lds + ((kt + 1) & 1) * Cfg::STAGE;
+        u32x4 ta[8], tb[8];
+        a.fetch(0, left_k, ta);
+        b.fetch(0, left_k, tb);
+        a.rest(left_k, ta, next);
+        b.rest(left_k, tb, next + Cfg::A_BYTES);
+      }
+      __syncthreads();
+    }
+    math.store(args, m0, n0, bz, scale);
+    return;
+  }
   for (int kt = -1; kt < nk; ++kt) {   // -1: the first stage's loads
     const int64_t left_k = K - (int64_t)(kt + 1) * BK;
     if (left_k > 0) {
