@@ -16,7 +16,10 @@ problems (section 4); the decision trees A/B/C and the MLP cost model are
 fitted on the training problems (section 5.1) and evaluated on the held-out
 test problems against exhaustive search (section 4.3).
 
-Prints one JSON line.  Only one GPU is supported: --gpus N > 1 exits.
+Prints one JSON line of the headline figures, short enough for a program that
+keeps only the end of the output (22 KB with every table in it); the full record
+goes to stderr as one line, and to a file with --detail.  Only one GPU is
+supported: --gpus N > 1 exits.
 """
 from __future__ import annotations
 
@@ -39,6 +42,34 @@ SEL_NAMES = {0: "DT-A", 1: "DT-B", 2: "DT-C", 3: "MLP"}
 
 def _log(*a):
     print(*a, file=sys.stderr, flush=True)
+
+
+CONTRACT = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better",
+            "scaling", "vs_baseline", "dtype", "data")
+
+
+def line_of(out):
+    """The printed line's record: the headline figures of a full one."""
+    line = {k: out[k] for k in CONTRACT}
+    c = out["config"]
+    line["config"] = {"workload": c["workload"], "problems": c["problems"],
+                      "gflop_per_step": c["gflop_per_step"], "k": c["k"], "selector": c["selector"]}
+    line["pct_mfma_peak"] = out["pct_mfma_peak"]
+    line["pct_of_optimal_test"] = out["deployed_pct_of_optimal_test"]["geomean"]
+    line["pct_of_exhaustive_best_live"] = out["pct_of_exhaustive_best"]["time_weighted_live_in_sample"]
+    line["selector_regret_test"] = {k: out["selector_regret_test"][k] for k in ("DT-B", "MLP")
+                                    if k in out["selector_regret_test"]}
+    line["roofline"] = out["roofline"]
+    if "cpu_baseline" in out:
+        line["cpu_baseline"] = {k: out["cpu_baseline"][k] for k in ("value", "unit", "cores", "kind")}
+    for name, lp in out.get("lowp", {}).items():
+        line[name] = {"tflops": lp["live_tflops"], "pct_of_optimal_test": lp["deployed_pct_of_optimal_test"],
+                      "speedup_vs_f32": lp["speedup_vs_f32_best_time_weighted"]}
+    if "vgg16" in out:
+        line["vgg16_ms"] = out["vgg16"]["ms_per_inference"]["selector"]
+    if "grouped_bf16" in out:
+        line["grouped_bf16_ms"] = out["grouped_bf16"]["rows_padded_16B"]["ms_per_launch"]
+    return line
 
 
 def _geomean(x):
@@ -913,6 +944,7 @@ def main(argv=None):
                     help="only the grouped BF16 section (for profiling its kernel)")
     ap.add_argument("--square-only", action="store_true",
                     help="only the BF16 / FP8 4096^3 section (for profiling its kernels)")
+    ap.add_argument("--detail", default=None, metavar="FILE", help="write the full record to FILE")
     a = ap.parse_args(argv)
     if a.calibrate_counters:
         calibrate_counters()
@@ -1331,7 +1363,11 @@ def main(argv=None):
         out["cpu_baseline"] = cpu_baseline(problems, a.cpu_budget_s,
                                            tuning=(T[tr_rows], tr_shapes, sel["norm"], k))
     h.close()
-    print(json.dumps(out), flush=True)
+    _log(json.dumps(out))
+    if a.detail:
+        with open(a.detail, "w") as f:
+            json.dump(out, f, indent=1)
+    print(json.dumps(line_of(out)), flush=True)
     return 0
 
 
