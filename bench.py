@@ -1061,9 +1061,13 @@ def main(argv=None):
     infer_mlp = None if a.step_only else \
         selection_latency(kt, h, torch, problems, stream)    # h holds the MLP here
     h.set_fallback(1)
+    # the conv table holds plain kernels unsliced, so the fallback's picks are
+    # timed in that form: without the workspace, kt_gemm(-1) slices nothing
+    h.set_workspace(None)
     conv = None if a.step_only else \
         conv_section(kt, h, tune, tune.table_path("f32", "conv"), (0, 1, 2, 3),
                      (tr_shapes, T[tr_rows], chosen, mws, mws_bytes, stream))
+    h.set_workspace(gemm_ws)
 
     # ---- the paper's comparison over the number of deployed kernels: for
     # each k, pruning (normalization chosen on the training rows), Top-N and
