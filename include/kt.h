@@ -383,7 +383,8 @@ kt_status kt_sweep_workspace_bytes(const kt_shape* shapes, int32_t n_shapes, kt_
  * operands are filled in the workspace, then each kernel is launched
  * `warmup` times and timed with HIP events over its reps (a split-K variant
  * as its slice launches plus reduction, its partial planes after the
- * operands in the workspace); the mean nanoseconds per launch go to
+ * operands in the workspace; a configuration unsliced, also where kt_gemm(-1)
+ * would run it in slices); the mean nanoseconds per launch go to
  * time_ns[shape * n_configs + c] (host, int64).  config_ids (host) selects
  * kernels (NULL = all kernels of the dtype, configurations and split-K
  * variants, in id order).  Entries already >= 0 in time_ns are kept

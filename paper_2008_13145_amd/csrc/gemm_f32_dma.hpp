@@ -120,12 +120,13 @@ __device__ __forceinline__ float f32_at_mnmajor(const float* t, int k, int col) 
 // A lane splits (64 + 64) * 16 / 64 values for 24 MFMAs a step: about 200
 // vector instructions (800 clocks) beside 768 clocks of MFMA, so the split of
 // step g + 1 is placed between the MFMAs of step g; one after the other the
-// two took turns (MFMA busy 50 %, now 57 %; the clock falls to 1.7 GHz under
-// this load, which bounds it).  Subtraction with a shift, not v_dot2_f32_bf16,
-// makes the residuals: the dot unit shares the matrix pipe.  32x32 wave blocks
-// (T = 4) split twice as many values per MFMA and gained nothing.
-// 128x128 tiles, BK = 32: 4096^3 NT 1051 -> 754 us (131 -> 182 TFLOP/s), NN
-// 1160 -> 758 us; 2048x1024x1536 batch 16 TN 813 -> 595 us.
+// two took turns.  Counters at 4096^3: MFMA busy 51 to 53 % of cycles at 1.8 to 1.95
+// GHz, to which the clock falls under this load.  Subtraction with a shift, not
+// v_dot2_f32_bf16, makes the residuals: the dot unit shares the matrix pipe.
+// 32x32 wave blocks (T = 4) split twice as many values per MFMA and gained
+// nothing.  128x128 tiles, BK = 32, with FP32 MFMAs -> this way on one card:
+// 4096^3 NT 1090 -> 776 us (126 -> 177 TFLOP/s), NN 1127 -> 777 us; 2048x1024x1536
+// batch 16 TN 880 -> 620 us.
 //
 // Two kinds of operand do not split: infinities and values that round to
 // infinity in BF16, whose residual is NaN, and values below 2^-110 (a NaN does:

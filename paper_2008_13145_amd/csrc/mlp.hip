@@ -137,9 +137,8 @@ __global__ void mlp_targets_kernel(const uint16_t* __restrict__ Xq, int n, int d
 // from a register lane by lane, so LDS carries one word per activation instead
 // of two per multiply.  Every sum runs in the order r or i = 0, 1, ... of its
 // block, one fused multiply-add each.  What bounds it is the chain of dependent
-// phases of one step, not the chip (of 26 k clocks, 9.6 k wait for the scalar loads
-// of W2, 6.6 k are the products over rows): so sixteen waves, two per unit of the
-// slice with one row block each.  3000 steps of 960 rows: 60 ms; eight waves that take
+// phases of one step, not the chip: so sixteen waves, two per unit of the slice
+// with one row block each.  3000 steps of 960 rows: 60 ms; eight waves that take
 // both blocks 71; one work-group per block that read both factors of every
 // multiply from LDS 113.
 static constexpr int MLP_SLICES = 8;

@@ -239,12 +239,13 @@ __device__ __forceinline__ void km_set_centroid(char* planes, int64_t* cc, int d
 // One restart per work-group.  Outputs in global memory: centroids
 // [restart][k][d], labels [restart][n], KmeansOut [restart].
 //
-// An iteration reads X once from L2 (960 x 188: 361 KB, about 2.6 us at one
-// CU's 64 B a clock), which bounds it; the products are 360 MFMAs.  Rows that
+// An iteration reads X ceil(k / 8) times from L2, once for each column tile (960 x
+// 188, k = 8: 361 KB, 2.4 us at one CU's 64 B a clock and 2.4 GHz); the products are
+// 360 MFMAs.  Rows that
 // change their cluster move between the member sums as they are found, so the
 // update costs the changed rows only (the sums are exact integers).  With 64-bit
 // vector arithmetic and a serial pass over the rows per dimension the same ten
-// restarts of 960 x 188, k = 8, took 32 ms.
+// restarts of 960 x 188, k = 8, took 33 ms, this way 1.5.
 __global__ void __launch_bounds__(KM_THREADS)
 kmeans_kernel(const uint16_t* __restrict__ X, int n, int d, int k, uint64_t seed, int max_iter,
               int64_t* __restrict__ g_cent, int32_t* __restrict__ g_labels,

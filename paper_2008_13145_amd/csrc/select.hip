@@ -198,7 +198,7 @@ static int64_t elem_bytes_sel(int dtype) { return dtype == KT_F32 ? 4 : dtype ==
 // converted for BF16 / FP8), split-K variants with scratch partial planes and
 // plain kernels in the slices that kt_gemm(-1) would run them in with the
 // workspace at hand (run_deep, its event included): one untimed launch, then
-// three timed ones each; the fastest (first on ties) wins.  Allocates the
+// three timed ones each, the faster ones twice; the fastest (first on ties) wins.  Allocates the
 // scratch on first use and synchronizes.
 static kt_status time_candidates(Ctx* h, int dtype, const kt_shape* s,
                                  const std::vector<int32_t>& cands, int32_t* out) {
