@@ -163,8 +163,9 @@ kt_status kt_gemm_workspace_bytes(kt_handle h, kt_dtype dtype, const kt_shape* s
  * The slices of deep FP32 products that the selector gives a plain kernel
  * (kt_gemm, kt_conv2d) take their planes from its end.  Those calls may be on
  * any streams: the handle orders them after one another, keeps them clear of
- * the part that split-K kernels have used and runs them unsplit under stream
- * capture.  That order is the handle's: give two handles two workspaces. */
+ * the parts that split-K kernels have used, of buffers set before as well, and
+ * runs them unsplit under stream capture (kt_gemm_splitk with a workspace of
+ * its own gives slices in a graph).  That order is the handle's: give two handles two workspaces. */
 kt_status kt_set_workspace(kt_handle h, void* workspace, size_t bytes);
 
 /* ------------------------------------------------------------------- GEMM */

@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 #include <string.h>
 
+#include <algorithm>
 #include <string>
 
 #include "kt_internal.hpp"
@@ -260,14 +261,15 @@ kt_status kt_set_workspace(kt_handle hh, void* workspace, size_t bytes) {
   h->gemm_ws = workspace;
   h->gemm_ws_bytes = workspace ? bytes : 0;
   if (!workspace) return KT_OK;
-  // where split-K kernels have been in the last buffer stays theirs in one
-  // that overlaps it; deep products may have been anywhere in the new one
-  const uintptr_t begin = (uintptr_t)workspace, end = begin + bytes, low_end = h->ws_begin + h->ws_low;
-  const bool overlap = begin < h->ws_end && h->ws_begin < end;
-  h->ws_low = overlap && low_end > begin ? low_end - begin : 0;
+  // where split-K kernels have been stays theirs (set again, the buffer may
+  // still be in use by them); deep products may have been anywhere in it
+  const uintptr_t begin = (uintptr_t)workspace, end = begin + bytes;
+  h->ws_low = 0;
+  for (int i = 0; i < h->split_spans; ++i) {
+    const Ctx::Span& s = h->split_used[i];
+    if (s.begin < end && begin < s.end) h->ws_low = std::max(h->ws_low, (size_t)(std::min(s.end, end) - begin));
+  }
   h->ws_high = h->deep_used ? bytes : 0;
-  h->ws_begin = begin;
-  h->ws_end = end;
   return KT_OK;
 }
 

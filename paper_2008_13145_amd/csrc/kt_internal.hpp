@@ -73,8 +73,10 @@ struct Ctx {
   size_t gemm_ws_bytes = 0;
   // Split-K kernels take its start, deep products of plain picks its end
   // (splitk.hip: run_deep).
-  uintptr_t ws_begin = 0, ws_end = 0;   // the last workspace set
-  size_t ws_low = 0;               // most bytes split-K kernels have taken from its start
+  struct Span { uintptr_t begin, end; };
+  Span split_used[16];             // where they have been, in all workspaces
+  int split_spans = 0;
+  size_t ws_low = 0;               // the same in the present one, bytes from its start
   size_t ws_high = 0;              // most bytes deep products have taken from its end
   hipEvent_t deep_done = nullptr;  // the last deep product in slices
   bool deep_used = false;          // deep_done has been recorded

@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <mutex>
 #include <string>
 
@@ -200,9 +201,32 @@ kt_status run_deep(Ctx* h, kt_dtype dtype, const kt_shape* s, float alpha, const
   return st;
 }
 
+// Remember that split-K kernels work in [begin, begin + bytes).  A program that
+// changes workspaces more often than there are places gets one span over all.
+static void split_was_in(Ctx* h, uintptr_t begin, size_t bytes) {
+  constexpr int MOST = sizeof h->split_used / sizeof h->split_used[0];
+  const uintptr_t end = begin + bytes;
+  for (int i = 0; i < h->split_spans; ++i)
+    if (h->split_used[i].begin == begin) {
+      h->split_used[i].end = std::max(h->split_used[i].end, end);
+      return;
+    }
+  if (h->split_spans == MOST) {
+    for (const Ctx::Span& s : h->split_used) {
+      h->split_used[0].begin = std::min(h->split_used[0].begin, s.begin);
+      h->split_used[0].end = std::max(h->split_used[0].end, s.end);
+    }
+    h->split_spans = 1;
+  }
+  h->split_used[h->split_spans++] = {begin, end};
+}
+
 kt_status order_split(Ctx* h, size_t bytes, hipStream_t stream) {
   if (bytes == 0 || !h->gemm_ws || h->gemm_ws_bytes < bytes) return KT_OK;   // runs unsplit
-  if (bytes > h->ws_low) h->ws_low = bytes;
+  if (bytes > h->ws_low) {
+    h->ws_low = bytes;
+    split_was_in(h, (uintptr_t)h->gemm_ws, bytes);
+  }
   if (!h->deep_used || bytes + h->ws_high <= h->gemm_ws_bytes) return KT_OK;
   hipStreamCaptureStatus capture;
   if (hipStreamIsCapturing(stream, &capture) != hipSuccess) {
